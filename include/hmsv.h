@@ -455,9 +455,9 @@ hmsv_status hmsv_p7_score(const hmsv_p7_profile *prof, const hmsv_db *db, int16_
  * p (hmsv_db_order maps p to the original id) of the sequences with flag
  * set or score >= threshold, in increasing p (so longest first), and their
  * number to *count (device int32).  Deterministic.  workspace:
- * hmsv_workspace_bytes(nseq) bytes, 256-byte aligned; it uses the part
- * that P7 calls leave alone, so the same workspace may serve the P7 call
- * that follows on the stream.  Asynchronous; allocates nothing.  score
+ * hmsv_workspace_bytes(nseq) bytes, 256-byte aligned; nothing in it is
+ * needed once the call is done, so the same workspace may serve the P7
+ * call that follows on the stream.  Asynchronous; allocates nothing.  score
  * and flags may be NULL for a database without sequences (*count = 0).
  * HMSV_EINVAL on null pointers, is_msv not 0/1 or a misaligned workspace,
  * HMSV_EDEVICE if a launch fails. */

@@ -1057,18 +1057,18 @@ hmsv_status p7_common(const hmsv_p7_profile *prof, const hmsv_db *db, const int3
     if (p7_lds_bytes(plan.G, plan.Q, db->table_rows) > (size_t)kLdsBytes) return HMSV_EUNSUPPORTED;
     if (db->nseq == 0) return HMSV_OK;       // nothing to write (outputs may be NULL)
     if (!score || !flags) return HMSV_EINVAL;
-    int blocks = plan.blocks;
-    if (blocks == 0) {
+    P7Blocks blocks{plan.blocks, plan.blocks};
+    if (plan.blocks == 0) {
         int dev = 0, cus = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return HMSV_EDEVICE;
-        const int per_cu = e->occupancy(plan.waves_per_block, db->table_rows);
-        if (per_cu <= 0) return HMSV_EDEVICE;
-        blocks = per_cu * cus;
+        const P7Blocks per_cu = e->occupancy(plan.waves_per_block, db->table_rows);
+        if (per_cu.general <= 0 || per_cu.fast <= 0) return HMSV_EDEVICE;
         const int64_t groups_per_block = (int64_t)plan.waves_per_block * (64 / plan.G);
         const int64_t need = (db->nseq + groups_per_block - 1) / groups_per_block;
-        if (need < blocks) blocks = (int)need;
+        blocks.general = (int)std::min<int64_t>(need, (int64_t)per_cu.general * cus);
+        blocks.fast = (int)std::min<int64_t>(need, (int64_t)per_cu.fast * cus);
     }
     P7Args a{};
     a.msc = prof->msc;
@@ -1083,7 +1083,10 @@ hmsv_status p7_common(const hmsv_p7_profile *prof, const hmsv_db *db, const int3
     a.score = score;
     a.flag = flags;
     a.image = (uint32_t *)((char *)workspace + kWsP7ImageOff);
+    a.fimage = (uint32_t *)((char *)workspace + kWsP7FImageOff);
     a.queue = (uint32_t *)((char *)workspace + kWsP7QueueOff);
+    a.fqueue = (uint32_t *)((char *)workspace + kWsP7FQueueOff);
+    a.pend = (int32_t *)((char *)workspace + kWsWinOff);
     a.aux = (int32_t *)workspace;
     a.rows = db->table_rows;
     a.sel = sel;
@@ -1116,8 +1119,8 @@ hmsv_status hmsv_select(const hmsv_db *db, const void *score, const uint8_t *fla
     if (((uintptr_t)workspace & 255u) != 0) return HMSV_EINVAL;
     if (db->nseq > 0 && (!score || !flags)) return HMSV_EINVAL;   // NULL only when empty
     if (db->nseq > (int64_t)INT32_MAX) return HMSV_EUNSUPPORTED;
-    // the per-block counts sit in the window area, which P7 calls leave alone
-    static_assert(kWsP7ImageOff + 160 * 1024 <= kWsWinOff, "selection scratch apart from P7");
+    // the per-block counts sit in the window area; they are not needed once
+    // the call is done
     int32_t *scratch = (int32_t *)((char *)workspace + kWsWinOff);
     if (select_scratch_bytes(db->nseq) > ws_bytes(db->nseq) - kWsWinOff) return HMSV_EINVAL;
     if (launch_select(db->d_seqs, db->nseq, score, flags, is_msv, threshold, positions, count,

@@ -178,6 +178,12 @@ inline int64_t plan_nodes(int G, int Q) { return (int64_t)2 * G * Q - 1; }
 // s's cells, so the ones into node s from node s-1 are stored shifted by
 // one slot.
 enum P7TransRow : int { kP7MMp = 0, kP7IMp, kP7DMp, kP7MI, kP7II, kP7MDp, kP7DDp };
+// The cost form's image (p7_fast.hpp): emission costs by residue, then these
+// transition rows.
+enum P7FastRow : int { kFMM = 0, kFMI, kFII, kFMD, kFDD, kFRows };
+inline size_t p7_fast_lds_bytes(int G, int Q, int rows) {
+    return (size_t)(rows + kFRows) * lds_layout(G, Q, kP7Rows).RS * 4;
+}
 
 struct P7Args {
     const int16_t *msc;    // [32][M] match emission scores (device)
@@ -192,9 +198,11 @@ struct P7Args {
     int16_t *score;
     uint8_t *flag;
     uint32_t *image;       // the LDS image (workspace)
-    int32_t *aux;          // workspace word: max over nodes of D->M (prep kernel)
+    uint32_t *fimage;      // the cost form's LDS image (workspace)
+    int32_t *aux;          // workspace words kAux..: the profile's bounds (prep kernel)
     uint32_t *queue;       // kP7Parts record queues, 128 bytes apart (zeroed by the
-                           // prep kernel)
+    uint32_t *fqueue;      // prep kernel); the cost form's kernel has its own
+    int32_t *pend;         // [nseq] positions the cost form leaves to p7_kernel (workspace)
     int32_t rows;          // emission rows (kRows or kDegenRows); the 7
                            // transition rows follow them
     const int32_t *sel;    // NULL: records 0..nseq-1; else the processing-order
@@ -211,17 +219,26 @@ hipError_t launch_select(const SeqRec *seqs, int64_t nseq, const void *score,
 
 constexpr int kMaxP7G = 64;
 constexpr int kP7Parts = 16;                 // record queues of a P7 call
-// P7 calls' workspace: aux word at 0, the queues from kWsCounterBytes, the
-// LDS image after them (P7 uses none of the MSV/SSV regions).
+// P7 calls' workspace: aux words at 0, the queues of both kernels from
+// kWsCounterBytes, their LDS images after them, the pending list in the
+// window area.
 constexpr size_t kWsP7QueueOff = kWsCounterBytes;
-constexpr size_t kWsP7ImageOff = kWsP7QueueOff + (size_t)kP7Parts * 128;
-static_assert(kWsP7ImageOff + 160 * 1024 <= kWsWinOff, "P7 image within the workspace");
-typedef hipError_t (*P7LaunchFn)(const P7Args &, int waves_per_block, int blocks, hipStream_t);
+constexpr size_t kWsP7FQueueOff = kWsP7QueueOff + (size_t)kP7Parts * 128;
+constexpr size_t kWsP7ImageOff = kWsP7FQueueOff + (size_t)kP7Parts * 128;
+constexpr size_t kWsP7FImageOff = kWsP7ImageOff + 160 * 1024;
+static_assert(kWsP7FImageOff + 160 * 1024 <= kWsWinOff, "P7 images within the workspace");
+// Blocks of a P7 call's two kernels.
+struct P7Blocks {
+    int general;
+    int fast;
+};
+typedef hipError_t (*P7LaunchFn)(const P7Args &, int waves_per_block, P7Blocks blocks, hipStream_t);
+typedef P7Blocks (*P7OccupancyFn)(int waves_per_block, int rows);
 struct P7KernelEntry {
     int G;
     int Q;
     P7LaunchFn launch;
-    OccupancyFn occupancy;
+    P7OccupancyFn occupancy;
 };
 int register_p7_kernels(const P7KernelEntry *entries, int n);
 

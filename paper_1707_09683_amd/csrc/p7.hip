@@ -2,7 +2,7 @@
 // HMSV_G and register counts Q in [HMSV_QLO, HMSV_QHI].  The build compiles
 // this file once per (G, Q-range) so the instantiations compile in parallel.
 #include <utility>
-#include "p7_kernel.hpp"
+#include "p7_fast.hpp"
 
 #if !defined(HMSV_G) || !defined(HMSV_QLO) || !defined(HMSV_QHI)
 #error "define HMSV_G, HMSV_QLO and HMSV_QHI"

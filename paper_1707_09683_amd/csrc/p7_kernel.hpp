@@ -55,6 +55,79 @@ constexpr int kP7Pos = 32767;
 constexpr int kP7Half = -32;          // E->J and E->C: 32 log2(1/2)
 __device__ __forceinline__ int sat16(int v) { return v < kP7Neg ? kP7Neg : (v > kP7Pos ? kP7Pos : v); }
 
+// The cost form of the recurrence (p7_fast.hpp): its frame rises by kP7Bias per
+// row and holds the floor at kP7Base at each step's start.
+constexpr int kP7Bias = 1024;         // largest emission score it takes (32 bits)
+constexpr int kP7MaxTbm = 4000;       // tBM in [-kP7MaxTbm, 0]
+constexpr int kP7MaxDm = 1900;        // D->M in [-kP7MaxDm, 0] at nodes with a D->D
+constexpr int kP7Dead = -20000;       // D->D at or below: -inf
+// 16 rows of bias and the steepest loop score (-64, L = 1) above 2048
+constexpr int kP7Base = 2048 + 16 * (kP7Bias + 64);
+// lvl = kP7Base + E->J half + move (L < 2^24: at least -717) + tBM must stay
+// below the fp16 infinity pattern
+static_assert(kP7Base + 32 + 720 + kP7MaxTbm < 0x7c00, "u stays a finite fp16 pattern");
+
+// Words of a call's workspace head (P7Args::aux), written by the prep kernel.
+constexpr int kAuxMaxDm = 0;      // max over nodes of D->M
+constexpr int kAuxTransOk = 1;    // transitions and tBM within the cost form's bounds
+constexpr int kAuxMinII = 2;      // smallest I->I cost over the nodes
+constexpr int kAuxRise = 3;       // largest sum of a run of D~->D~ scores (0 if none is above)
+constexpr int kAuxPend = 4;       // records the cost form leaves to p7_kernel
+constexpr int kAuxEmisOk = 8;     // per emission row: no score above kP7Bias
+static_assert((kAuxEmisOk + kDegenRows) * 4 <= (int)kWsCounterBytes, "aux words fit");
+
+// Whether the cost form holds for the call's profile (the same for every
+// wavefront of the launch).
+__device__ __forceinline__ bool p7_profile_fast(const P7Args &a) {
+    const int lane = threadIdx.x & 63;
+    bool bad = a.aux[kAuxTransOk] == 0;
+    if (lane < a.rows) bad = bad || a.aux[kAuxEmisOk + lane] == 0;
+    return !__any(bad);
+}
+
+// Record queues.  Records come from queues (counters the prep kernel
+// zeroed), longest first: a lane group claims a record as it starts one, so
+// a group that drew a long sequence draws fewer others.  Blocks are spread
+// over up to kP7Parts queues, each on its own 128-byte line: queue p hands
+// out records p, p + P, p + 2P, ... (each longest first), so one counter's
+// atomics come from a fraction of the grid.  A claim is taken (its value
+// broadcast from the group's first lane) only at the group's next switch, by
+// when it has returned: `issue` for the groups that claim, `take` by the
+// whole wavefront.
+template <int G>
+struct P7Queue {
+    int nparts, part, lane, j;
+    uint32_t *ctr;
+    uint32_t craw = 0u;
+
+    __device__ P7Queue(uint32_t *queues, int lane_, int j_) : lane(lane_), j(j_) {
+        nparts = (int)(gridDim.x < (unsigned)kP7Parts ? gridDim.x : (unsigned)kP7Parts);
+        part = (int)(blockIdx.x % (unsigned)nparts);
+        ctr = queues + part * 32;
+    }
+    __device__ __forceinline__ void issue(bool want) {    // called by the whole wavefront
+        // one atomic per wavefront (by lane 0) for all of its claiming
+        // groups, each group's claim its rank among them
+        const bool w = want && j == 0;
+        const unsigned long long m = __ballot(w);
+        if (m == 0ull) return;
+        uint32_t base = 0u;
+        if (lane == 0) base = atomicAdd(ctr, (uint32_t)__popcll(m));
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (w) craw = base + rank;
+    }
+    // a processing position, or -1: none left
+    __device__ __forceinline__ int take(const int32_t *sel, int nseq) {
+        int k = (int)craw;
+        if constexpr (G > 1) k = __shfl(k, lane - j);
+        const long long r = (long long)part + (long long)nparts * (long long)k;
+        if (r >= (long long)nseq) return -1;
+        return sel ? sel[r] : (int)r;
+    }
+};
+
 // Score of table row r (emissions by residue below a.rows, transitions
 // from there) at slot s (node s; slot 0 is the dummy).
 __device__ __forceinline__ int p7_slot_score(const P7Args &a, int r, int s) {
@@ -73,32 +146,126 @@ __device__ __forceinline__ int p7_slot_score(const P7Args &a, int r, int s) {
     return a.trans[row * M + from - 1];
 }
 
-// The LDS image (a.rows + 7 rows of the lds_layout(G, Q, kP7Rows) shape),
-// one dword per thread.
+// Cost (u16, 65535 for none) of a score <= add.
+__device__ __forceinline__ uint32_t p7_cost(int score, int add) {
+    const int v = add - score;
+    return (uint32_t)(v < 0 ? 0 : v > 65535 ? 65535 : v);
+}
+
+// Entry of the cost image (see p7_fast.hpp) of table row r at slot s (node s;
+// slot 0 is the dummy): emission costs below a.rows, then the transition
+// rows kFMM.. : M->M into s; M->I~ and I~->I~ at s; M->D~ and D~->D~ into s.
+// I~ and D~ include I->M and D->M out of their node.
+__device__ __forceinline__ uint32_t p7_slot_cost(const P7Args &a, int r, int s) {
+    const int M = a.M;
+    const bool node = s >= 1 && s <= M;
+    if (r < a.rows)
+        return !node || r == kInvalidCode ? 65535u : p7_cost(a.msc[r * M + s - 1], kP7Bias);
+    auto tr = [&](int row, int k) -> int { return a.trans[row * M + k - 1]; };   // out of node k
+    const int t = r - a.rows;
+    const bool from = s >= 2 && s <= M;      // a node s - 1 leads to node s
+    switch (t) {
+    case kFMM: return from ? p7_cost(tr(0, s - 1), 0) : 65535u;
+    case kFMI: return node ? p7_cost(tr(1, s) + tr(3, s), kP7Bias) : 65535u;
+    case kFII: return node ? p7_cost(tr(4, s), kP7Bias) : 65535u;
+    case kFMD: return from && tr(5, s) >= -kP7MaxDm ? p7_cost(tr(2, s - 1) + tr(5, s), 0) : 65535u;
+    default: {
+        // D~ of s from D~ of s - 1: a score (s16), the nodes' D->M exchanged
+        if (!from || tr(6, s - 1) <= kP7Dead || tr(5, s - 1) < -kP7MaxDm || tr(5, s) < -kP7MaxDm)
+            return (uint16_t)(short)kP7Neg;
+        return (uint16_t)(short)(tr(6, s - 1) + tr(5, s) - tr(5, s - 1));
+    }
+    }
+}
+
+// Per call: the LDS images (general_rows = a.rows + 7 rows of scores, and
+// a.rows + kFRows rows of the cost form, both of the lds_layout(G, Q,
+// kP7Rows) shape), one dword per thread; then one block for the profile's
+// transitions and one per emission row: what the cost form's bounds need.
 template <int G, int Q>
-__global__ void __launch_bounds__(256) p7_prep_kernel(P7Args a, int image_blocks) {
+__global__ void __launch_bounds__(256) p7_prep_kernel(P7Args a, int image_blocks,
+                                                      int fimage_blocks) {
     constexpr LdsLayout D = lds_layout(G, Q, kP7Rows);
-    if ((int)blockIdx.x == image_blocks) {
-        // the last block: max over nodes of D->M into aux[0]
-        __shared__ int red[256];
-        int m = kP7Neg;
-        for (int k = threadIdx.x; k < a.M; k += 256) {
-            const int v = a.trans[5 * a.M + k];
-            m = v > m ? v : m;
-        }
-        red[threadIdx.x] = m;
-        __syncthreads();
-        for (int h = 128; h > 0; h >>= 1) {
-            if ((int)threadIdx.x < h && red[threadIdx.x + h] > red[threadIdx.x])
-                red[threadIdx.x] = red[threadIdx.x + h];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) a.aux[0] = red[0];
-        if (threadIdx.x < kP7Parts) a.queue[threadIdx.x * 32] = 0u;   // the record queues
+    const int check0 = image_blocks + fimage_blocks;
+    if ((int)blockIdx.x > check0) {
+        const int x = (int)blockIdx.x - check0 - 1;       // emission row
+        bool big = false;
+        if (x != kInvalidCode)
+            for (int k = threadIdx.x; k < a.M; k += 256) big = big || a.msc[x * a.M + k] > kP7Bias;
+        if (!__syncthreads_or(big) && threadIdx.x == 0) a.aux[kAuxEmisOk + x] = 1;
+        else if (threadIdx.x == 0) a.aux[kAuxEmisOk + x] = 0;
         return;
     }
-    const int idx = (int)(blockIdx.x * 256 + threadIdx.x);
-    if (idx >= (a.rows + 7) * D.RS) return;
+    if ((int)blockIdx.x == check0) {
+        // the transitions: max of D->M, smallest I->I cost, the range of D->M
+        // over the nodes with a finite one, and whether all are within the
+        // bounds
+        __shared__ int red[4][256];
+        auto top = [&](int t) {                   // red[t][0] = the maximum
+            __syncthreads();
+            for (int h = 128; h > 0; h >>= 1) {
+                if ((int)threadIdx.x < h && red[t][threadIdx.x + h] > red[t][threadIdx.x])
+                    red[t][threadIdx.x] = red[t][threadIdx.x + h];
+                __syncthreads();
+            }
+            return red[t][0];
+        };
+        int m = kP7Neg, mii = 65535, dlo = 0, dhi = -kP7MaxDm;
+        bool bad = a.tbm > 0 || a.tbm < -kP7MaxTbm;
+        for (int k = threadIdx.x; k < a.M; k += 256) {
+            const int dm = a.trans[5 * a.M + k], dd = a.trans[6 * a.M + k];
+            const int ii = -(int)a.trans[4 * a.M + k];
+            m = dm > m ? dm : m;
+            mii = ii < mii ? ii : mii;
+            if (dm >= -kP7MaxDm) {
+                dlo = dm < dlo ? dm : dlo;
+                dhi = dm > dhi ? dm : dhi;
+            } else if (dd > kP7Dead) {
+                bad = true;
+            }
+#pragma unroll
+            for (int t = 0; t < 7; ++t) bad = bad || a.trans[t * a.M + k] > 0;
+        }
+        red[0][threadIdx.x] = m;
+        red[1][threadIdx.x] = -mii;
+        red[2][threadIdx.x] = -dlo;
+        red[3][threadIdx.x] = dhi;
+        bad = __syncthreads_or(bad);
+        const int maxdm = top(0), minii = -top(1), span = top(2) + top(3);
+        // the largest sum of a run of D~->D~ scores.  D->D scores are at most 0, so
+        // no run adds more than the range of D->M: a start is done when what
+        // it lost exceeds that.
+        int rise = 0;
+        if (!bad) {
+            for (int k = threadIdx.x; k < a.M; k += 256) {
+                int sum = 0;
+                for (int s = k + 2; s <= a.M && sum + span > rise; ++s) {
+                    const int d = (short)p7_slot_cost(a, a.rows + kFDD, s);
+                    if (d == kP7Neg) break;
+                    sum += d;
+                    rise = sum > rise ? sum : rise;
+                }
+            }
+        }
+        __syncthreads();
+        red[0][threadIdx.x] = rise;
+        const int most = top(0);
+        if (threadIdx.x == 0) {
+            a.aux[kAuxMaxDm] = maxdm;
+            a.aux[kAuxTransOk] = bad ? 0 : 1;
+            a.aux[kAuxMinII] = minii;
+            a.aux[kAuxRise] = most;
+            a.aux[kAuxPend] = 0;
+        }
+        if (threadIdx.x < kP7Parts) {                       // the record queues
+            a.queue[threadIdx.x * 32] = 0u;
+            a.fqueue[threadIdx.x * 32] = 0u;
+        }
+        return;
+    }
+    const bool cost = (int)blockIdx.x >= image_blocks;
+    const int idx = (int)((blockIdx.x - (cost ? image_blocks : 0)) * 256 + threadIdx.x);
+    if (idx >= (a.rows + (cost ? (int)kFRows : 7)) * D.RS) return;
     const int x = idx / D.RS;
     int rem = idx - x * D.RS;
     int w, q0;
@@ -122,17 +289,31 @@ __global__ void __launch_bounds__(256) p7_prep_kernel(P7Args a, int image_blocks
     const int s0 = qq + Q * (2 * jj);
     uint32_t v = 0u;
     if (qq < Q) {
-        const uint32_t lo = (uint16_t)(short)p7_slot_score(a, x, s0);
-        const uint32_t hi = (uint16_t)(short)p7_slot_score(a, x, s0 + Q);
+        const uint32_t lo = cost ? p7_slot_cost(a, x, s0) : (uint16_t)(short)p7_slot_score(a, x, s0);
+        const uint32_t hi = cost ? p7_slot_cost(a, x, s0 + Q)
+                                 : (uint16_t)(short)p7_slot_score(a, x, s0 + Q);
         v = lo | (hi << 16);
     }
-    a.image[idx] = v;
+    (cost ? a.fimage : a.image)[idx] = v;
 }
 
 template <int G, int Q, int THREADS>
 __global__ void __launch_bounds__(THREADS) p7_kernel(P7Args a) {
     using Lay = Layout<G, Q, kP7Rows>;
     constexpr int RS = Lay::RS;
+    // Records: the whole database (processing positions 0..nseq-1), or the
+    // positions a selection pass left in sel[0 .. *nsel) (a device count,
+    // known only here; never more than the database holds); or, where the cost
+    // form holds for the profile, the few that its kernel left.
+    const bool rest = p7_profile_fast(a);
+    const int32_t *sel = rest ? a.pend : a.sel;
+    const int nseq = rest ? a.aux[kAuxPend] : sel ? min(*a.nsel, a.nseq) : a.nseq;
+    if (rest) {
+        // the first blocks are enough (at least one per queue)
+        const int per = (int)(blockDim.x / G);
+        const int need = (nseq + per - 1) / per;
+        if (nseq == 0 || (int)blockIdx.x >= (need > kP7Parts ? need : kP7Parts)) return;
+    }
     extern __shared__ uint32_t lds[];
     {
         const uint4 *src = (const uint4 *)a.image;
@@ -141,7 +322,7 @@ __global__ void __launch_bounds__(THREADS) p7_kernel(P7Args a) {
         for (int i = threadIdx.x; i < n16; i += blockDim.x) dst[i] = src[i];
     }
     __syncthreads();
-    const int maxdm = a.aux[0];       // max over nodes of D->M (prep kernel)
+    const int maxdm = a.aux[kAuxMaxDm];       // max over nodes of D->M (prep kernel)
 
     const int lane = threadIdx.x & 63;
     const int j = lane % G;
@@ -166,47 +347,11 @@ __global__ void __launch_bounds__(THREADS) p7_kernel(P7Args a) {
     };
     const uint32_t rT = (uint32_t)a.rows;    // first transition row
 
-    // Records: the whole database (processing positions 0..nseq-1), or the
-    // positions a selection pass left in sel[0 .. *nsel) (a device count,
-    // known only here; never more than the database holds).
-    const int32_t *sel = a.sel;
-    const int nseq = sel ? min(*a.nsel, a.nseq) : a.nseq;
-    // Records come from queues (counters the prep kernel zeroed), longest
-    // first: a lane group claims a record as it starts one, so a group that
-    // drew a long sequence draws fewer others.  Blocks are spread over up to
-    // kP7Parts queues, each on its own 128-byte line: queue p hands out
-    // records p, p + P, p + 2P, ... (each longest first), so one counter's
-    // atomics come from a fraction of the grid.  A claim is taken (its value
-    // broadcast from the group's first lane) only at the group's next
-    // switch, by when it has returned: `issue` for the groups that claim,
-    // `take` by the whole wavefront.
-    const int nparts = (int)(gridDim.x < (unsigned)kP7Parts ? gridDim.x : (unsigned)kP7Parts);
-    const int part = (int)(blockIdx.x % (unsigned)nparts);
-    uint32_t *ctr = a.queue + part * 32;
-    uint32_t craw = 0u;
-    auto issue = [&](bool want) {    // called by the whole wavefront
-        // one atomic per wavefront (by lane 0) for all of its claiming
-        // groups, each group's claim its rank among them
-        const bool w = want && gstart;
-        const unsigned long long m = __ballot(w);
-        if (m == 0ull) return;
-        uint32_t base = 0u;
-        if (lane == 0) base = atomicAdd(ctr, (uint32_t)__popcll(m));
-        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
-        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
-            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        if (w) craw = base + rank;
-    };
-    auto take = [&]() -> int {    // a processing position, or -1: none left
-        int k = (int)craw;
-        if constexpr (G > 1) k = __shfl(k, lane - j);
-        const long long r = (long long)part + (long long)nparts * (long long)k;
-        if (r >= (long long)nseq) return -1;
-        return sel ? sel[r] : (int)r;
-    };
+    P7Queue<G> queue(a.queue, lane, j);
+    auto take = [&]() -> int { return queue.take(sel, nseq); };
 
     s16x2 Mr[Q], Ir[Q], Dr[Q];
-    issue(true);
+    queue.issue(true);
     int t = take();
     uint4 rec = make_uint4(0u, 0u, 0u, 0u), rec16 = rec;
     uint32_t lm = 0u;
@@ -216,7 +361,7 @@ __global__ void __launch_bounds__(THREADS) p7_kernel(P7Args a) {
         lm = a.lenmodel[t];
     }
     // the next record, claimed and loaded while the current one runs
-    issue(true);
+    queue.issue(true);
     int tn = take();
     uint4 nrec = rec, nrec16 = rec16;
     uint32_t nlm = lm;
@@ -260,7 +405,7 @@ __global__ void __launch_bounds__(THREADS) p7_kernel(P7Args a) {
     };
     start();
     prefetch();
-    issue(true);                 // the record after that, taken at the switch
+    queue.issue(true);           // the record after that, taken at the switch
 
     for (;;) {
         if (!__any(active)) break;
@@ -434,68 +579,8 @@ __global__ void __launch_bounds__(THREADS) p7_kernel(P7Args a) {
             start();
             prefetch();
         }
-        issue(ended);
+        queue.issue(ended);
     }
-}
-
-// Blocks of up to 8 wavefronts (512 threads), or 16 for 64-lane groups
-// whose kernel fits the 128 VGPRs of a 1024-thread block without spilling
-// (Q <= 18 and Q = 20; the compiler spills 20-40 bytes per lane at Q = 19,
-// 21 and 22): their LDS image allows one block per CU, so 16 wavefronts per
-// block is the way to 4 per SIMD.
-template <int G, int Q>
-constexpr int kP7MaxWaves = (G == 64 && (Q <= 18 || Q == 20)) ? 16 : 8;
-
-template <int G, int Q, int THREADS>
-hipError_t launch_p7_kernel(const P7Args &a, int wpb, int blocks, hipStream_t s) {
-    const size_t lds = p7_lds_bytes(G, Q, a.rows);
-    if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)p7_kernel<G, Q, THREADS>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL((p7_kernel<G, Q, THREADS>), dim3(blocks), dim3(wpb * 64), lds, s, a);
-    return hipGetLastError();
-}
-
-// The LDS image, then the filter kernel.
-template <int G, int Q>
-hipError_t launch_p7(const P7Args &a, int wpb, int blocks, hipStream_t s) {
-    if (a.rows != kRows && a.rows != kDegenRows) return hipErrorInvalidValue;
-    const int n = (a.rows + 7) * lds_layout(G, Q, kP7Rows).RS;
-    if (wpb < 1 || wpb > kP7MaxWaves<G, Q>) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((p7_prep_kernel<G, Q>), dim3((n + 255) / 256 + 1), dim3(256), 0, s, a,
-                       (n + 255) / 256);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if constexpr (kP7MaxWaves<G, Q> > 8) {
-        if (wpb > 8) return launch_p7_kernel<G, Q, 1024>(a, wpb, blocks, s);
-    }
-    return launch_p7_kernel<G, Q, 512>(a, wpb, blocks, s);
-}
-
-template <int G, int Q, int THREADS>
-int occupancy_p7_kernel(int wpb, int rows) {
-    int nb = 0;
-    const size_t lds = p7_lds_bytes(G, Q, rows);
-    if (hipFuncSetAttribute((const void *)p7_kernel<G, Q, THREADS>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-        return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, p7_kernel<G, Q, THREADS>, wpb * 64,
-                                                     lds) != hipSuccess)
-        return 0;
-    return nb;
-}
-
-// Resident blocks of wpb wavefronts per CU (0 on error or an unsupported
-// block size).
-template <int G, int Q>
-int occupancy_p7(int wpb, int rows) {
-    if (wpb < 1 || wpb > kP7MaxWaves<G, Q>) return 0;
-    if constexpr (kP7MaxWaves<G, Q> > 8) {
-        if (wpb > 8) return occupancy_p7_kernel<G, Q, 1024>(wpb, rows);
-    }
-    return occupancy_p7_kernel<G, Q, 512>(wpb, rows);
 }
 
 }  // namespace hmsv
