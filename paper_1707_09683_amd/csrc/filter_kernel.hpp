@@ -123,6 +123,17 @@ __device__ __forceinline__ int group_max(int m) {
     return m;
 }
 
+// Unsigned minimum and maximum over the group (a signed max of the flipped
+// complement, and of the flipped value).
+template <int G>
+__device__ __forceinline__ uint32_t group_first(uint32_t v) {
+    return ~((uint32_t)group_max<G>((int)(~v ^ 0x80000000u)) ^ 0x80000000u);
+}
+template <int G>
+__device__ __forceinline__ uint32_t group_last(uint32_t v) {
+    return (uint32_t)group_max<G>((int)(v ^ 0x80000000u)) ^ 0x80000000u;
+}
+
 // fp16 pattern -> integer filter value u (exact: u/1024 is representable).
 __device__ __forceinline__ int bits_to_units(int bits) {
     _Float16 h = __builtin_bit_cast(_Float16, (unsigned short)bits);
@@ -219,7 +230,8 @@ struct Lane {
         update(c);
     }
 
-    // The cell update of one row, given the row's scores.
+    // The cell update of one row, given the row's scores: in place, registers
+    // in descending order (register q takes the old q - 1).
     __device__ __forceinline__ void update(const uint32_t (&c)[Q]) {
         uint32_t gam = shift_in(R[Q - 1]);
         uint32_t prev_v = 0;
@@ -248,8 +260,8 @@ enum Mode : int {
     kMSV = 1,      // MSV (Alg. 2) with scB fixed
 };
 
-// Counters in the workspace.
-constexpr int kCtrMain = 0;      // next sequence of the range
+// Residue words (four residues each) per load and lane.
+constexpr int kWords = 4;
 
 // Flag value that marks a sequence whose score the exact pass still owes.
 constexpr uint8_t kFlagPending = 2;
@@ -263,8 +275,7 @@ constexpr uint32_t kNoStep = 0xffffffffu;
 // base + tec without overflow), its rescoring window for the exact pass:
 // `warm` rows before the first loud step (not before the sequence's start)
 // to the end of the last one, never past send; the whole sequence if no
-// step was loud.  K: words of four residues per step of the filter kernel.
-template <int K>
+// step was loud.
 __device__ __forceinline__ void msv_settle(const KArgs &a, uint32_t sid, int mx,
                                            uint32_t wfirst, uint32_t wlast, uint32_t sstart,
                                            uint32_t send, uint32_t tjb) {
@@ -279,7 +290,7 @@ __device__ __forceinline__ void msv_settle(const KArgs &a, uint32_t sid, int mx,
     const uint32_t w = (uint32_t)a.warm;
     const bool known = wfirst != kNoStep && wfirst < send;
     const uint32_t ws = known && wfirst >= sstart + w ? (wfirst - w) & ~15u : sstart;
-    uint32_t we = known ? wlast + 4u * K : send;
+    uint32_t we = known ? wlast + 4u * kWords : send;
     we = we < send ? we : send;
     a.win[sid] = make_uint4(ws, (we - ws) | (tjb << 24), sid, 0u);
     a.flag[sid] = kFlagPending;
@@ -293,10 +304,6 @@ constexpr int kExitGroups = G == 1 ? 8 : G == 2 ? 4 : G == 4 ? 2 : 1;
 // Lanes with at most this many registers read each row's scores one row
 // ahead (a second set of Q registers).
 constexpr int kPipeQ = 17;
-
-// Residue words (four residues each) per load and lane: 16 or 8 residues.
-template <int G>
-constexpr int kWordsPerLoad = G <= 8 ? 4 : 2;
 
 // One filter launch.  Every lane group pulls sequences (longest first)
 // from the call's range and runs their rows in steps of 4K residues.
@@ -372,14 +379,13 @@ filter_kernel(KArgs a) {
     uint32_t first_loud = kNoStep, last_loud = 0u;
     bool active = false;
     bool need = false;           // group wants a sequence
-    // Residues come in words of four, K words per load (16 residues for
-    // groups of up to 8 lanes, 8 for wider ones): each group streams its own
-    // sequence, and a load issued 4K rows before its first use hides the
-    // memory latency of the first touch of each line.  Sequences then run
-    // in whole 4K-row steps (the extra rows are non-scoring padding, which
-    // cannot change a score).
-    constexpr int K = kWordsPerLoad<G>;
-    uint32_t wv[K];              // next 4K residues of the group's sequence
+    // Residues come in words of four, four words per load: each group streams
+    // its own sequence, and a load issued 16 rows before its first use hides
+    // the memory latency of the first touch of each line.  Sequences then run in
+    // whole 16-row steps (the extra rows are non-scoring padding, which cannot
+    // change a score).
+    constexpr int K = kWords;
+    uint32_t wv[K];              // this step's 16 residues of the group's sequence
 #pragma unroll
     for (int k = 0; k < K; ++k) wv[k] = 0u;
 
@@ -395,59 +401,72 @@ filter_kernel(KArgs a) {
     // lane that issued it (pend_b, in lane pend_first) until the next switch
     // of the wavefront resolves it.
     //
-    // Queue positions map to records so that the grid's N groups start on
-    // the N longest sequences and each holds two of the shortest as A and
-    // qc: positions [0, N) are records [0, N), positions [N, 3N) the last
-    // 2N records (shortest first from the end), positions from 3N (claimed
-    // dynamically) the records in between, longest first.  No group thus
-    // queues a long sequence behind its first one.  Ranges with fewer than
-    // 3N records use positions as record numbers (so a group whose number is
-    // at least the record count never gets one).
-    const bool tail = nv >= 3 * ngroups;
-    constexpr int kNone = 0x7fffffff;             // position past the range
-    auto record_of = [&](int p) -> int {          // queue position -> record
-        if (p >= nv) return kNone;
-        if (!tail || p < ngroups) return p;
-        if (p < 3 * ngroups) return nv - 1 - (p - ngroups);
-        return p - 2 * ngroups;
+    // Which records the grid's N groups take.  Records run longest first, and
+    // a group's next two are fixed when it starts: group g starts with record
+    // g; the first nlong groups go on with the shortest records; the others
+    // with the next longest, the group of the shortest first record taking the
+    // longest of them (twice).  The records in between are claimed as groups
+    // finish, longest first.  The host sets nlong (plan_split): N where most
+    // records are claimed, and where few are, the groups whose first record is
+    // a large part of the mean work per group, so that what is fixed adds up to
+    // about the same for each.  (All in the order of the first ones: SSV at
+    // M = 30, 500,000 sequences 222 us, in this order 210; M = 64 397 and 365.)
+    constexpr int kNone = 0x7fffffff;
+    const int nlong = a.nlong;
+    const int i2 = 2 * ngroups - nlong;           // end of the second ones in order
+    const int i3 = i2 + ngroups - nlong;          // and of the third ones
+    auto second = [&](int g) -> int {
+        const int r = g < nlong ? nv - 1 - g : 2 * ngroups - 1 - g;
+        return g < nlong ? (r >= i2 ? r : kNone) : (r < nv ? r : kNone);
+    };
+    auto third = [&](int g) -> int {
+        const int r = g < nlong ? nv - 1 - nlong - g : i2 + ngroups - 1 - g;
+        return g < nlong ? (r >= i3 ? r : kNone) : (r < nv - nlong ? r : kNone);
+    };
+    // Claims come from up to kQueues counters, each on its own 128-byte line:
+    // counter p hands out records p, p + P, ... of those in between to 1/P of the
+    // blocks.  One counter takes an atomic every 2 to 4 ns, which bounded calls
+    // with many short rows: SSV at M = 100, 500,000 sequences with 16 counters
+    // 1.73x as fast on 64-lane groups, 1.67x on 32, 1.51x on 16, 1.30x on 8.
+    // A call that needs no claims makes none.
+    const int parts = (int)gridDim.x < kQueues ? (int)gridDim.x : kQueues;
+    const int part = (int)blockIdx.x % parts;
+    uint32_t *counter = a.counter + part * 32;
+    const bool claims = i3 < nv - 2 * nlong;
+    auto claimed = [&](int k) -> int {
+        const int r = i3 + part + parts * k;
+        return r < nv - 2 * nlong ? r : kNone;
     };
     auto fetch = [&](int r, uint4 &h, uint4 &f) {
         r = r < nv ? r : nv - 1;
         const uint4 *p = r < nsegs ? segs + 2 * r : recs + 2 * (r - nsegs + nsplit);
         h = p[0];
-        if constexpr (K > 1) f = p[1];
+        f = p[1];
     };
     // the residue words at offset o
     auto load_words = [&](uint32_t o, uint32_t (&d)[K]) {
-        if constexpr (K == 4) {
-            uint4 v = *(const uint4 *)(a.res + o);
-            d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-        } else if constexpr (K == 2) {
-            uint2 v = *(const uint2 *)(a.res + o);
-            d[0] = v.x; d[1] = v.y;
-        } else {
-            d[0] = *(const uint32_t *)(a.res + o);
-        }
+        uint4 v = *(const uint4 *)(a.res + o);
+        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
     };
     uint4 ra;                    // record A: off, rows | tjb << 24, id, length
-    uint4 ra16;                  // record A's first sixteen residues (K > 1)
+    uint4 ra16;                  // record A's first sixteen residues
     int qa, qc;                  // records of A and of the claimed position (kNone: none)
     uint32_t pend_b = 0;
     int pend_first = -1;         // wave-uniform
     auto start_record = [&](const uint4 &r, const uint4 &r16, bool valid) {
         active = valid;
-        uint32_t rows = r.y & kRowsMask;
-        if constexpr (K > 1) rows = (rows + 4u * K - 1u) & ~(4u * K - 1u);
+        const uint32_t rows = ((r.y & kRowsMask) + 15u) & ~15u;
         seq_off = valid ? r.x : a.pad_off;
         seq_end = valid ? r.x + rows : a.pad_off;
         id = r.z;
         tjbm = (int)(r.y >> 24) + a.tbm;
-        static_assert(K == 4 || K == 2, "residues come 16 or 8 per load");
-        if constexpr (K == 4) {
-            wv[0] = r16.x; wv[1] = r16.y; wv[2] = r16.z; wv[3] = r16.w;
-        } else {
-            wv[0] = r16.x; wv[1] = r16.y;
-        }
+        wv[0] = r16.x; wv[1] = r16.y; wv[2] = r16.z; wv[3] = r16.w;
+    };
+    // the offset after o's step: where a group that parks at its end has none,
+    // the non-scoring residues after the database
+    auto next_off = [&](uint32_t o) -> uint32_t {
+        const uint32_t n = o + (active ? 16u : 0u);
+        return kExitGroups<G> > 1 && n >= seq_end ? a.pad_off : n;
     };
 
     // MSV running max with scB fixed: max over the lane group of its cells'
@@ -482,12 +501,12 @@ filter_kernel(KArgs a) {
     };
 
     {
-        int q0 = record_of(gid);
+        const int q0 = gid < nv ? gid : kNone;
         uint4 r0, r016 = {0u, 0u, 0u, 0u};
         fetch(q0, r0, r016);
-        qa = record_of(ngroups + gid);
+        qa = second(gid);
         fetch(qa, ra, ra16);
-        qc = record_of(2 * ngroups + gid);
+        qc = third(gid);
         start_record(r0, r016, q0 != kNone);
         start_sequence();
     }
@@ -499,7 +518,7 @@ filter_kernel(KArgs a) {
             // group with a pending claim holds -1 - its rank in qc
             if (pend_first >= 0) {
                 int b = __builtin_amdgcn_readlane((int)pend_b, pend_first);
-                if (qc < 0) qc = record_of(3 * ngroups + b - 1 - qc);
+                if (qc < 0) qc = claimed(b - 1 - qc);
             }
             if (need) {
                 start_record(ra, ra16, qa != kNone);
@@ -508,13 +527,17 @@ filter_kernel(KArgs a) {
             }
             fetch(qa, ra, ra16);
             // new claims for the groups that just switched
-            unsigned long long m = __ballot(need && gstart);
-            int first = __ffsll((long long)m) - 1;
-            if (lane == first) pend_b = atomicAdd(a.counter + kCtrMain, (uint32_t)__popcll(m));
-            pend_first = first;
-            // the group's rank: claiming groups below its first lane
-            int rank = __popcll(m & ((1ull << (lane - j)) - 1ull));
-            if (need) qc = -1 - rank;
+            if (claims) {
+                unsigned long long m = __ballot(need && gstart);
+                int first = __ffsll((long long)m) - 1;
+                if (lane == first) pend_b = atomicAdd(counter, (uint32_t)__popcll(m));
+                pend_first = first;
+                // the group's rank: claiming groups below its first lane
+                int rank = __popcll(m & ((1ull << (lane - j)) - 1ull));
+                if (need) qc = -1 - rank;
+            } else if (need) {
+                qc = kNone;
+            }
             need = false;
         }
         if (!__any(active)) break;
@@ -528,7 +551,6 @@ filter_kernel(KArgs a) {
         // switch code once per several sequence ends.
         const int n_act = __popcll(__ballot(active && gstart));
         const int e_min = n_act < kExitGroups<G> ? n_act : kExitGroups<G>;
-        const uint32_t step = active ? 4u * K : 0u;
         bool ended = false;
         // Short rows are latency bound when a wavefront runs alone (the
         // last, longest sequences of a launch): their scores are read one
@@ -538,10 +560,9 @@ filter_kernel(KArgs a) {
         auto xrow = [&](int r) -> uint32_t { return (wv[r / 4] >> (8 * (r % 4))) & 0xffu; };
         if constexpr (PIPE) st.load_row(T[0], T[1], T[2], xrow(0), ca);
         do {
-            uint32_t offn = off + step;
-            if constexpr (kExitGroups<G> > 1) offn = offn < seq_end ? offn : a.pad_off;
+            const uint32_t offn = next_off(off);
             uint32_t wn[K];
-            load_words(offn, wn);                                    // next 4K residues
+            load_words(offn, wn);                                    // next 16 residues
             // one residue row
             auto one_row = [&](auto r_c) {
                 constexpr int r = decltype(r_c)::value;
@@ -622,13 +643,9 @@ filter_kernel(KArgs a) {
                 int v = xb + bst;
                 mx = v > 0 ? v : 0;
             }
-            // the group's first and last loud steps (unsigned min by a signed
-            // max of the flipped complement, unsigned max by a signed max of
-            // the flipped value); called by whole wavefronts
-            const uint32_t gfirst =
-                ~((uint32_t)group_max<G>((int)(~first_loud ^ 0x80000000u)) ^ 0x80000000u);
-            const uint32_t glast =
-                (uint32_t)group_max<G>((int)(last_loud ^ 0x80000000u)) ^ 0x80000000u;
+            // the group's first and last loud steps; called by whole wavefronts
+            const uint32_t gfirst = group_first<G>(first_loud);
+            const uint32_t glast = group_last<G>(last_loud);
             // A segment stores its maximum and loud steps for
             // combine_msv_kernel, which settles its sequence after this
             // kernel; a whole sequence settles here.
@@ -639,8 +656,8 @@ filter_kernel(KArgs a) {
                     x[2] = gfirst;
                     x[3] = glast;
                 } else {
-                    msv_settle<K>(a, id, mx, gfirst, glast, seq_off, seq_end,
-                                  (uint32_t)(tjbm - a.tbm));
+                    msv_settle(a, id, mx, gfirst, glast, seq_off, seq_end,
+                               (uint32_t)(tjbm - a.tbm));
                 }
             }
             need = ended;
@@ -671,7 +688,7 @@ __device__ __forceinline__ void build_segment(const KArgs &a, int p) {
     const uint32_t T = (uint32_t)a.seg_rows;
     const uint32_t beg = (uint32_t)s * T;
     const uint32_t end = beg + T < rows ? beg + T : rows;
-    const uint32_t st = s == 0 ? 0u : beg - (uint32_t)a.warm;
+    const uint32_t st = beg > (uint32_t)a.warm ? beg - (uint32_t)a.warm : 0u;
     const uint32_t off = r.off + st;
     const uint4 w = *(const uint4 *)(a.res + off);
     uint4 *d = (uint4 *)(a.segs + p);
@@ -685,45 +702,65 @@ __device__ __forceinline__ void build_segment(const KArgs &a, int p) {
     }
 }
 
-// SSV: score and flag of each split sequence from its segments' maxima
-// (one thread each).
+// Lanes that combine one split sequence: its segments are read kCombine at a
+// time (one thread per sequence read them one after the other, 0.4 us each: 27
+// us for the 55 segments of a sequence of 7,000 residues; now 6).
+constexpr int kCombine = 16;
+
+// SSV: score and flag of each split sequence from its segments' maxima.
 static __global__ void __launch_bounds__(256) combine_kernel(KArgs a) {
-    const int t = (int)(blockIdx.x * 256 + threadIdx.x);
-    if (t >= a.nsplit) return;
-    const uint32_t *sl = a.slots + kSlotWords * t;
-    const uint32_t v = sl[0], id = sl[2], p = sl[5];
-    uint32_t m = 0;
-    for (uint32_t k = 0; k < v; ++k) {
-        uint32_t x = a.segx[4 * (p + k)];
+    const int t = (int)((blockIdx.x * 256 + threadIdx.x) / kCombine);
+    const uint32_t j = threadIdx.x % kCombine;
+    uint32_t v = 0, id = 0, p = 0;
+    if (t < a.nsplit) {
+        const uint32_t *sl = a.slots + kSlotWords * t;
+        v = sl[0];
+        id = sl[2];
+        p = sl[5];
+    }
+    int m = 0;
+    for (uint32_t k = j; k < v; k += kCombine) {
+        const int x = (int)a.segx[4 * (p + k)];
         m = x > m ? x : m;
     }
-    bool of = m >= 255;
-    a.score[id] = of ? (uint8_t)127 : (uint8_t)(int8_t)((int)m - 128);
+    m = group_max<kCombine>(m);
+    if (t >= a.nsplit || j != 0) return;
+    const bool of = m >= 255;
+    a.score[id] = of ? (uint8_t)127 : (uint8_t)(int8_t)(m - 128);
     a.flag[id] = of ? 1 : 0;
 }
 
-// MSV: settle each split sequence from its segments (one thread each): the
-// maximum over them (every cell of the sequence lies in some segment's own
-// rows, and warm-up cells never exceed the true ones) and the earliest and
-// latest loud steps; then score and flag, or a rescoring window, as for a
-// whole sequence.  Runs between the filter kernel and the exact pass.
-template <int K>
-__global__ void __launch_bounds__(256) combine_msv_kernel(KArgs a) {
-    const int t = (int)(blockIdx.x * 256 + threadIdx.x);
-    if (t >= a.nsplit) return;
-    const uint32_t *sl = a.slots + kSlotWords * t;
-    const uint32_t v = sl[0], sid = sl[2], rec = sl[3], p = sl[5];
+// MSV: settle each split sequence from its segments: the maximum over them
+// (every cell of the sequence lies in some segment's own rows, and warm-up
+// cells never exceed the true ones) and the earliest and latest loud steps;
+// then score and flag, or a rescoring window, as for a whole sequence.  Runs
+// between the filter kernel and the exact pass.
+static __global__ void __launch_bounds__(256) combine_msv_kernel(KArgs a) {
+    const int t = (int)((blockIdx.x * 256 + threadIdx.x) / kCombine);
+    const uint32_t j = threadIdx.x % kCombine;
+    uint32_t v = 0, sid = 0, rec = 0, p = 0;
+    if (t < a.nsplit) {
+        const uint32_t *sl = a.slots + kSlotWords * t;
+        v = sl[0];
+        sid = sl[2];
+        rec = sl[3];
+        p = sl[5];
+    }
     int mx = 0;
     uint32_t wfirst = kNoStep, wlast = 0u;
-    for (uint32_t k = 0; k < v; ++k) {
+    for (uint32_t k = j; k < v; k += kCombine) {
         const uint4 x = *(const uint4 *)(a.segx + 4 * (p + k));
         mx = (int)x.x > mx ? (int)x.x : mx;
         wfirst = x.z < wfirst ? x.z : wfirst;
         wlast = x.w > wlast ? x.w : wlast;
     }
+    mx = group_max<kCombine>(mx);
+    wfirst = group_first<kCombine>(wfirst);
+    wlast = group_last<kCombine>(wlast);
+    if (t >= a.nsplit || j != 0) return;
     const SeqRec &r = a.seqs[rec];
-    const uint32_t send = r.off + (((r.rt & kRowsMask) + 4u * K - 1u) & ~(4u * K - 1u));
-    msv_settle<K>(a, sid, mx, wfirst, wlast, r.off, send, r.rt >> 24);
+    const uint32_t send = r.off + (((r.rt & kRowsMask) + 15u) & ~15u);
+    msv_settle(a, sid, mx, wfirst, wlast, r.off, send, r.rt >> 24);
 }
 
 // One dword of a profile's LDS image for a lane group of G lanes with Q
@@ -759,7 +796,7 @@ __device__ __forceinline__ uint32_t image_dword(const KArgs &a, const LdsLayout 
 }
 
 // Per call: the filter kernel's LDS image of the profile and, for MSV, the
-// exact pass's image (Layout<64, qx>); threads 0..3 reset the counters.
+// exact pass's image (Layout<64, qx>); the first threads reset the queue counters.
 // For MSV, a.rows more blocks compute best[x] = max_k (dbias - cost_k(x)).
 // The last blocks build the records and slots of split sequences.
 template <int G, int Q, bool MSV>
@@ -800,7 +837,7 @@ __global__ void __launch_bounds__(256) prep_kernel(KArgs a, int image_blocks, in
         return;
     }
     const int idx = b * 256 + (int)threadIdx.x;
-    if (idx < 4) a.counter[idx] = 0u;
+    if (idx < kQueues) a.counter[idx * 32] = 0u;
     if (idx < a.rows * D.RS) a.image[idx] = image_dword<MSV>(a, D, G, Q, idx);
 }
 
@@ -1039,13 +1076,15 @@ hipError_t launch_filter(const KArgs &a, int wpb, int blocks, hipStream_t s) {
     if constexpr (MSV) {
         e = launch_filter_mode<G, Q, kMSV>(a, wpb, blocks, s);
         if (e != hipSuccess || a.nsplit == 0) return e;
-        hipLaunchKernelGGL(combine_msv_kernel<kWordsPerLoad<G>>, dim3((a.nsplit + 255) / 256),
+        hipLaunchKernelGGL(combine_msv_kernel,
+                           dim3((a.nsplit * kCombine + 255) / 256),
                            dim3(256), 0, s, a);
         return hipGetLastError();
     }
     e = launch_filter_mode<G, Q, kSSV>(a, wpb, blocks, s);
     if (e != hipSuccess || a.nsplit == 0) return e;
-    hipLaunchKernelGGL(combine_kernel, dim3((a.nsplit + 255) / 256), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(combine_kernel, dim3((a.nsplit * kCombine + 255) / 256), dim3(256), 0, s,
+                       a);
     return hipGetLastError();
 }
 

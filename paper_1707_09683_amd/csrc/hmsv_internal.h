@@ -45,9 +45,10 @@ constexpr uint32_t kSegBit = 0x80000000u;     // record is a segment (ids stay b
 // original id, record, -, first segment, -, -}.  The segments store their
 // results and a small kernel combines them after the filter kernel (for
 // MSV it also decides whether the sequence needs an exact rescoring).
-constexpr int kMaxSegs = 1 << 17;     // segment records per call
+constexpr int kSegRoom = 1 << 17;     // their records' room, the last 64 taken by the queues
+constexpr int kMaxSegs = kSegRoom - 64;   // segment records per call
 constexpr int kMaxSplit = 1 << 16;    // split sequences per call
-constexpr int kMaxBins = 32;          // distinct segment counts per call
+constexpr int kMaxBins = 64;          // distinct segment counts per call
 constexpr int kSlotWords = 8;
 
 struct KArgs {
@@ -62,7 +63,8 @@ struct KArgs {
     uint32_t pad_off;      // offset of >= 16 non-scoring residues
     uint8_t *score;
     uint8_t *flag;
-    uint32_t *counter;     // work-queue head, zeroed by the prep kernel
+    uint32_t *counter;     // kQueues work-queue heads, 128 bytes apart (zeroed by the
+                           // prep kernel)
     uint32_t *image;       // LDS image of the profile (workspace), 16-byte aligned
     int32_t *best;         // MSV: per table row, max over nodes of dbias - cost (workspace)
     int32_t rows;          // table rows of the LDS images: kRows or kDegenRows
@@ -80,6 +82,8 @@ struct KArgs {
     int32_t nsegs;
     int32_t seg_rows;      // rows per segment (multiple of 16)
     int32_t warm;          // rows before a segment (multiple of 16, >= M - 1)
+    int32_t nlong;         // groups whose first record is a large part of the mean
+                           // work per group (at most the grid's groups)
     // Split sequence t has v = ceil(rows / seg_rows) segments, which take
     // records p .. p + v - 1.  Records are longest first, so v only falls
     // with t: bin b covers t >= bin_t[b] with v = bin_v[b] and
@@ -90,16 +94,19 @@ struct KArgs {
     int32_t bin_v[kMaxBins];
 };
 
-// Workspace layout: queue counters (bytes 0..63), the MSV per-residue best
-// scores (bytes 64..147), the profile's LDS image from byte 256, then the
-// segment records, the split-sequence slots, the MSV exact pass's LDS
+// Workspace layout: the MSV per-residue best scores (bytes 64..171), the
+// profile's LDS image from byte 256, then the segment records, the queue
+// counters, the split-sequence slots, the MSV exact pass's LDS
 // image and a 16-byte window record per sequence of the database (by
 // original index).
 constexpr size_t kWsCounterBytes = 256;
 constexpr size_t kWsSegOff = kWsCounterBytes + 160 * 1024;
-constexpr size_t kWsSlotOff = kWsSegOff + (size_t)kMaxSegs * sizeof(SeqRec);
+constexpr int kQueues = 16;
+constexpr size_t kWsQueueOff = kWsSegOff + (size_t)kMaxSegs * sizeof(SeqRec);
+constexpr size_t kWsSlotOff = kWsSegOff + (size_t)kSegRoom * sizeof(SeqRec);
+static_assert(kWsQueueOff % 128 == 0 && kWsQueueOff + kQueues * 128 <= kWsSlotOff, "queue lines");
 constexpr size_t kWsSegxOff = kWsSlotOff + (size_t)kMaxSplit * kSlotWords * 4;
-constexpr size_t kWsXImageOff = kWsSegxOff + (size_t)kMaxSegs * 16;
+constexpr size_t kWsXImageOff = kWsSegxOff + (size_t)kSegRoom * 16;
 static_assert(kWsSegxOff % 16 == 0, "segment words are read as uint4");
 constexpr size_t kWsWinOff = kWsXImageOff + 160 * 1024;
 constexpr size_t ws_bytes(int64_t nseq) { return kWsWinOff + 16 * (size_t)(nseq > 1 ? nseq : 1); }
@@ -150,7 +157,10 @@ constexpr LdsLayout lds_layout(int G, int Q, int rows = kRows) {
     LdsLayout L{};
     L.CW = lds_copies(G, 4) * G * 4;
     int nf = Q / 4, r = Q % 4;
-    L.WIDE = r != 0 && (size_t)rows * (size_t)(nf + 1) * (size_t)L.CW * 4 <= kLdsBytes;
+    // (one or two registers alone: reading 4 or 8 bytes of 16 would take the
+    // LDS four or two passes)
+    L.WIDE = r != 0 && (nf > 0 || r == 3) &&
+             (size_t)rows * (size_t)(nf + 1) * (size_t)L.CW * 4 <= kLdsBytes;
     L.NF = L.WIDE ? nf + 1 : nf;
     L.R = L.WIDE ? 0 : r;
     L.OFF2 = L.NF * L.CW;
