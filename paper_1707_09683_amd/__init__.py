@@ -354,8 +354,6 @@ def _score(filt, profile: Profile, db: Database, score, flags, workspace, plan, 
             raise ValueError("all tensors must be on the profile's device")
     if stream is None:
         stream = torch.cuda.current_stream(dev)
-    if plan is None:
-        plan = db_default_plan(db, filt, profile.M)
     pl = ctypes.byref(plan) if plan is not None else None
     with torch.cuda.device(dev):
         if rng is None:

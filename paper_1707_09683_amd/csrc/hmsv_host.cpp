@@ -208,31 +208,164 @@ hmsv_status check_plan(const hmsv_plan *pl, int M, int rows = kRows) {
     return HMSV_OK;
 }
 
-// The plan of a call on a database whose images need `rows` table rows:
-// the caller's, or the default; if the default's image does not fit the
-// LDS with the degenerate rows, the narrowest lane group whose image does.
-// MSV also needs the exact pass's image (64-lane groups) to fit.
-hmsv_status resolve_plan(int is_msv, int M, int rows, const hmsv_plan *in, hmsv_plan *out) {
-    if (is_msv && lds_bytes(kExactG, exact_q(M), rows) > (size_t)kLdsBytes)
-        return HMSV_EUNSUPPORTED;
+// ---- what a call's rows cost ------------------------------------------------
+// A model of the filter kernel's time, in shader cycles, for choosing how a
+// call is cut and how wide its lane groups are.  Its figures are a fit to 2,850
+// timed SSV calls (M = 30 to 2400, 2,000 to 500,000 sequences, every group
+// width, cuts at eight lengths; 11% rms error on the faster ones); what it
+// chooses takes 2.8% more time on average than the fastest of those, 18% at
+// most.
+//  * a row of a wavefront takes 6.3 Q + 13.5 cycles of its SIMD (Q registers
+//    per lane), 11% more where scores come through a ring, 15% more with
+//    64-lane groups (their scores come in up to three pieces);
+//  * alone on its SIMD, a wavefront takes 31 + 10.5 Q cycles per row (the chain
+//    from one row to the next and the reads of scores); a record longer than
+//    the mean work per group adds 0.6 of that per row beyond it;
+//  * a sequence's end stops its wavefront for 105 cycles per wavefront on the
+//    SIMD.
+constexpr double kSimds = 1024.0;            // 256 CUs x 4
+double row_issue(int G, int Q) {
+    return (6.3 * Q + 13.5) * (Q > 32 ? 1.11 : 1.0) * (G == 64 ? 1.15 : 1.0);
+}
+double row_alone(int G, int Q) { return (31.0 + 10.5 * Q) * (G == 64 ? 1.15 : 1.0); }
+
+// Rows of records [0, t) of a range, and of record t.
+struct Range {
+    const int64_t *cum;
+    int64_t count;
+    int64_t rows(int64_t t) const { return cum[t + 1] - cum[t]; }
+    int64_t upto(int64_t t) const { return cum[t] - cum[0]; }
+    // records of more than r rows (they come first: longest first)
+    int64_t above(int64_t r) const {
+        int64_t lo = 0, hi = count;
+        while (lo < hi) {
+            const int64_t m = (lo + hi) / 2;
+            if (rows(m) > r) lo = m + 1;
+            else hi = m;
+        }
+        return lo;
+    }
+};
+
+// How a call's longest sequences are cut: those of more than `limit` rows, into
+// segments of `seg` rows (0: none); and the time that is expected of it.
+struct Cut {
+    int64_t limit = 0;
+    int64_t seg = 0;
+    double cycles = 0.0;
+};
+
+// Shorter segments are not worth their record.
+constexpr int64_t kMinSeg = 288;
+// The kernel that combines segments (4 us), and a segment's record.
+constexpr double kCutCycles = 9000.0, kSegCycles = 2.5;
+
+// The cut of a range for lane groups of G lanes, Q registers, at most ngroups
+// of them resident.  A launch ends no earlier than its longest record, which
+// one lane group runs at the speed of a lone wavefront once the others are
+// done: records above the mean work per group (total rows / lane groups) are
+// cut, down to the length at which the rows that segments repeat (warm =
+// M - 1 rounded up to 16 before each) cost more than the wait they save.
+Cut choose_cut(const Range &r, int M, int G, int Q, int64_t ngroups) {
+    const int64_t warm = ((M - 1) + 15) & ~15;
+    const int64_t total = r.upto(r.count), longest = r.rows(0);
+    const double issue = row_issue(G, Q), alone = row_alone(G, Q);
+    const double batch = G == 1 ? 8.0 : G == 2 ? 4.0 : G == 4 ? 2.0 : 1.0;   // ends per stop
+    const double mean0 = (double)total / (double)std::max<int64_t>(1, std::min(ngroups, r.count));
+    Cut best;
+    for (int k = -1; k < 10; ++k) {
+        Cut c;
+        int64_t ns = 0, segs = 0, top = longest;
+        if (k >= 0) {
+            // limits 2, 1.41, 1, 0.71, ... times the mean work per group
+            c.limit = (int64_t)(mean0 * std::pow(2.0, 1.0 - 0.5 * k)) & ~(int64_t)15;
+            c.seg = std::max(c.limit - warm, std::max(kMinSeg, warm / 4)) & ~(int64_t)15;
+            c.limit = std::max(c.limit, c.seg);
+            if (c.limit >= longest) continue;
+            ns = r.above(c.limit);
+            if (ns > kMaxSplit || r.upto(ns) / c.seg + ns > kMaxSegs) break;
+            if (longest / c.seg > kMaxBins && ns > kMaxBins) break;
+            segs = r.upto(ns) / c.seg + ns / 2 + 1;
+            top = std::max(c.limit, c.seg + warm);
+        }
+        const double nrec = (double)(r.count - ns + segs);
+        const double rows = (double)total + (double)(segs - ns) * (double)warm + 8.0 * nrec;
+        const double n = std::min((double)ngroups, nrec);
+        const double waves = std::max(1.0, n * G / 64.0);
+        const double share = std::max(1.0, waves / kSimds);      // wavefronts per SIMD
+        const double mean = rows / n;
+        c.cycles = mean * std::max(alone, issue * share) * (share > 1.5 ? 1.04 : 1.0) +
+                   0.6 * std::max(0.0, (double)top - mean) * alone +
+                   nrec / waves / batch * 105.0 * share +
+                   (ns > 0 ? kCutCycles + kSegCycles * (double)segs : 0.0);
+        if (k < 0 || c.cycles < best.cycles) best = c;
+    }
+    return best;
+}
+
+// Wavefronts of a plan that fit a CU, by LDS and by registers (about Q + 60
+// per lane, 512 per SIMD lane): an estimate that queries no device.
+int resident_waves(int G, int Q, int wpb, int rows) {
+    const int by_lds = (int)((size_t)kLdsBytes / std::max<size_t>(1, lds_bytes(G, Q, rows))) * wpb;
+    const int by_regs = Q <= 13 ? 20 : Q <= 60 ? 16 : 12;
+    return std::max(wpb, std::min(by_lds, by_regs / wpb * wpb));
+}
+
+// Wavefronts per block of an untuned plan: four, one per SIMD, where several
+// images fit a CU.  (The wavefronts of a block start on neighbouring records,
+// so large blocks put the longest ones on the same CU: M = 2400 on 60,000
+// sequences 1.45 ms with 8 wavefronts, 1.69 with 12, 2.03 with 16.)
+int block_waves(int G, int Q, int rows) { return lds_bytes(G, Q, rows) > 40 * 1024 ? 8 : 4; }
+
+// The plan of a call on a range of a database whose images need `rows` table
+// rows: the caller's, or else the lane group width of the least expected time.
+// The tuned plan (measured on 500,000 sequences) stays unless another is
+// expected to be at least 5% faster: the model ranks widths within a few
+// percent, and on large databases the measured order is the better one.  On
+// small ones wide groups win (fewer rows in sequence, and more wavefronts):
+// M = 400 on 5,000 sequences 284 us with the tuned 8 lanes, 111 with 64;
+// M = 151 on 20,000 107 with 4 lanes, 75 with 8.  The image of 64-lane groups
+// must fit (MSV's exact pass runs on it), which bounds M for both filters.
+hmsv_status resolve_plan(int is_msv, int M, int rows, const Range &r, const hmsv_plan *in,
+                         hmsv_plan *out) {
+    if (lds_bytes(kExactG, exact_q(M), rows) > (size_t)kLdsBytes) return HMSV_EUNSUPPORTED;
     if (in) {
         *out = *in;
         return check_plan(out, M, rows);
     }
-    hmsv_status st = hmsv_default_plan(is_msv, M, out);
+    hmsv_plan tuned;
+    hmsv_status st = hmsv_default_plan(is_msv, M, &tuned);
     if (st != HMSV_OK) return st;
-    if (lds_bytes(out->G, out->Q, rows) <= (size_t)kLdsBytes) return check_plan(out, M, rows);
+    double best = 0.0;
+    bool any = false;
     for (int G : {1, 2, 4, 8, 16, 32, 64}) {
-        const int Q = (M + 1 + 2 * G - 1) / (2 * G);
-        if (Q > 32 || lds_bytes(G, Q, rows) > (size_t)kLdsBytes) continue;
-        if (!registry().find(is_msv ? 1 : 0, G, Q)) continue;
-        out->G = G;
-        out->Q = Q;
-        out->waves_per_block = lds_bytes(G, Q, rows) > 48 * 1024 ? 8 : 4;
-        out->blocks = 0;
-        return check_plan(out, M, rows);
+        hmsv_plan p;
+        p.G = G;
+        p.Q = (M + 1 + 2 * G - 1) / (2 * G);
+        if (lds_bytes(G, p.Q, rows) > (size_t)kLdsBytes) continue;
+        if (!registry().find(is_msv ? 1 : 0, G, p.Q)) continue;
+        const bool is_tuned = G == tuned.G && p.Q == tuned.Q;
+        p.waves_per_block = is_tuned ? tuned.waves_per_block : block_waves(G, p.Q, rows);
+        p.blocks = 0;
+        double t = 0.0;
+        if (r.count > 0) {
+            int64_t waves = 256 * resident_waves(G, p.Q, p.waves_per_block, rows);
+            if (is_tuned && r.upto(r.count) < waves * (64 / G) * r.rows(0)) {
+                // the longest records set the end: see block_waves
+                p.waves_per_block = std::min(p.waves_per_block, block_waves(G, p.Q, rows));
+                waves = 256 * resident_waves(G, p.Q, p.waves_per_block, rows);
+            }
+            t = choose_cut(r, M, G, p.Q, waves * (64 / G)).cycles * (is_tuned ? 0.95 : 1.0);
+        } else if (!is_tuned) {
+            t = (double)G;              // nothing to score: the tuned plan, or the narrowest
+        }
+        if (!any || t < best) {
+            any = true;
+            best = t;
+            *out = p;
+        }
     }
-    return HMSV_EUNSUPPORTED;
+    return any ? check_plan(out, M, rows) : HMSV_EUNSUPPORTED;
 }
 
 // Blocks of a call's launch: the plan's, or a persistent grid of the
@@ -250,52 +383,50 @@ int grid_blocks(const KernelEntry *e, const hmsv_plan &plan, int64_t count, int 
     return blocks;
 }
 
-// Which sequences of a call's range [first, first + count) to split, for
-// ngroups lane groups and profile length M.  A launch ends no earlier than
-// its longest sequence, which one lane group runs at the speed of a
-// wavefront sharing its SIMD; sequences well above the mean work per group
-// (total rows / ngroups) are therefore cut into segments of about that
-// many rows.  Segments carry M - 1 warm-up rows (rounded up to 16), so
-// segments are at least four times that long, and their number is capped.
-void plan_split(const hmsv_db *db, int64_t first, int64_t count, int64_t ngroups, int M,
-                KArgs &a) {
+// Which sequences of a call's range [first, first + count) to split
+// (choose_cut), as the table of segment counts the kernels read, and the
+// blocks of its grid: segments may fill more lane groups than there are
+// sequences.
+void plan_split(const hmsv_db *db, int64_t first, int64_t count, const KernelEntry *e,
+                const hmsv_plan &plan, int M, int *blocks, KArgs &a) {
     a.nsplit = 0;
     a.nsegs = 0;
     a.nbins = 0;
     a.warm = ((M - 1) + 15) & ~15;
     a.seg_rows = 0;
-    a.nlong = 0;
-    const int64_t *cum = db->cum_rows.data() + first;
-    const int64_t total = cum[count] - cum[0];
-    if (ngroups <= 0 || count < 2) return;
-    int64_t T = std::max<int64_t>({total / ngroups, 4 * (int64_t)a.warm, 256});
-    T = (T + 15) & ~(int64_t)15;
-    for (; T < (int64_t)kRowsLimit; T *= 2) {
-        // split the sequences above 1.5 T (they come first: longest first)
-        const int64_t thr = T + T / 2;
-        int64_t ns = 0, segs = 0, bins = 0, prev_v = -1;
-        bool fits = true;
-        while (ns < count && cum[ns + 1] - cum[ns] > thr) {
-            int64_t v = (cum[ns + 1] - cum[ns] + T - 1) / T;
-            if (v != prev_v) {
-                if (bins == kMaxBins) { fits = false; break; }
-                a.bin_t[bins] = (int32_t)ns;
+    const int64_t per_block = (int64_t)plan.waves_per_block * (64 / plan.G);
+    int most = *blocks;                       // blocks the launch may have
+    if (plan.blocks == 0) most = resident_blocks(e, plan.waves_per_block, db->table_rows);
+    if (most < *blocks) most = *blocks;
+    const Range r{db->cum_rows.data() + first, count};
+    const Cut c = count < 2 ? Cut{} : choose_cut(r, M, plan.G, plan.Q, (int64_t)most * per_block);
+    int64_t T = c.seg, limit = c.limit;
+    for (; T > 0 && T < (int64_t)kRowsLimit; T *= 2, limit *= 2) {
+        const int64_t ns = r.above(limit);
+        int64_t t = 0, segs = 0, bins = 0;
+        while (t < ns && bins <= kMaxBins) {
+            // records from t on with as many segments as t has
+            const int64_t v = (r.rows(t) + T - 1) / T;
+            const int64_t e2 = std::min(ns, r.above((v - 1) * T));
+            if (bins < kMaxBins) {
+                a.bin_t[bins] = (int32_t)t;
                 a.bin_p[bins] = (int32_t)segs;
                 a.bin_v[bins] = (int32_t)v;
-                ++bins;
-                prev_v = v;
             }
-            segs += v;
-            ++ns;
-            if (ns > kMaxSplit || segs > kMaxSegs) { fits = false; break; }
+            ++bins;
+            segs += v * (e2 - t);
+            t = e2;
         }
-        if (!fits) continue;
+        if (bins > kMaxBins || ns > kMaxSplit || segs > kMaxSegs) continue;
         a.nsplit = (int32_t)ns;
         a.nsegs = (int32_t)segs;
         a.nbins = (int32_t)bins;
         a.seg_rows = (int32_t)T;
         break;
     }
+    const int64_t nrec = count - a.nsplit + a.nsegs;
+    if (plan.blocks == 0)
+        *blocks = (int)std::min<int64_t>(most, (nrec + per_block - 1) / per_block);
     // Groups that start on a record of more than half the mean work go on with
     // the shortest records.  With six or more
     // records per group all do: wavefronts advance unequally (the oldest of a
@@ -303,17 +434,12 @@ void plan_split(const hmsv_db *db, int64_t first, int64_t count, int64_t ngroups
     // records.  M = 400, 500,000 sequences (15 per group): 1784 us by the first
     // rule, 1709 by the second; M = 1000, 100,000 (12): 877 and 846; M = 128,
     // 250,000 (4): 374 and 388.
-    const int64_t half = (total + (int64_t)(a.nsegs - a.nsplit) * a.warm) / ngroups / 2;
-    int64_t nl = 0, hi = count;                     // records of more than `half` rows
-    while (nl < hi) {
-        const int64_t m = (nl + hi) / 2;
-        if (cum[m + 1] - cum[m] > half) nl = m + 1;
-        else hi = m;
-    }
-    nl = std::max<int64_t>(nl - a.nsplit, 0);
+    const int64_t groups = *blocks * per_block;
+    const int64_t half = (r.upto(count) + (int64_t)(a.nsegs - a.nsplit) * a.warm) / groups / 2;
+    int64_t nl = r.above(half) - a.nsplit;
+    if (nl < 0) nl = 0;
     if (a.seg_rows + a.warm > half) nl += a.nsegs;
-    const int64_t nrec = count - a.nsplit + a.nsegs;
-    a.nlong = (int32_t)(nrec >= 6 * ngroups ? ngroups : std::min(nl, ngroups));
+    a.nlong = (int32_t)(nrec >= 6 * groups ? groups : std::min(nl, groups));
 }
 
 hmsv_status score_common(int is_msv, const hmsv_profile *prof, const hmsv_db *db,
@@ -328,13 +454,16 @@ hmsv_status score_common(int is_msv, const hmsv_profile *prof, const hmsv_db *db
         st = check_plan(plan_in, prof->M);
         if (st != HMSV_OK) return st;
     }
+    if (count == -1 && first == 0) count = db->nseq;      // whole database
+    const bool in_range = first >= 0 && count >= 0 && first <= db->nseq && count <= db->nseq - first;
     hmsv_plan plan;
-    st = resolve_plan(is_msv, prof->M, db->table_rows, plan_in, &plan);
+    st = resolve_plan(is_msv, prof->M, db->table_rows,
+                      Range{db->cum_rows.data() + (in_range ? first : 0), in_range ? count : 0},
+                      plan_in, &plan);
     if (st != HMSV_OK) return st;
     const KernelEntry *e = registry().find(is_msv, plan.G, plan.Q);
     if (!e) return HMSV_ENOKERNEL;
-    if (count == -1 && first == 0) count = db->nseq;      // whole database
-    if (first < 0 || count < 0 || first > db->nseq || count > db->nseq - first) return HMSV_EINVAL;
+    if (!in_range) return HMSV_EINVAL;
     if (count == 0) return HMSV_OK;          // nothing to write (outputs may be NULL)
     if (!score || !flags) return HMSV_EINVAL;
 
@@ -362,10 +491,9 @@ hmsv_status score_common(int is_msv, const hmsv_profile *prof, const hmsv_db *db
     a.rows = db->table_rows;
     if (((uintptr_t)workspace & 255u) != 0) return HMSV_EINVAL;
 
-    const int blocks = grid_blocks(e, plan, count, db->table_rows);
+    int blocks = grid_blocks(e, plan, count, db->table_rows);
     if (blocks <= 0) return HMSV_EDEVICE;
-    plan_split(db, first, count, (int64_t)blocks * plan.waves_per_block * (64 / plan.G),
-               prof->M, a);
+    plan_split(db, first, count, e, plan, prof->M, &blocks, a);
     // MSV: a second kernel rescores the windows the first one stored
     ExactLaunchFn xf = nullptr;
     int cus = 0;
@@ -801,7 +929,8 @@ int32_t hmsv_db_table_rows(const hmsv_db *db) { return db ? db->table_rows : -1;
 hmsv_status hmsv_db_default_plan(const hmsv_db *db, int32_t is_msv, int32_t M, hmsv_plan *plan) {
     if (!db || !plan || M < 1) return HMSV_EINVAL;
     if (M > HMSV_MAX_M) return HMSV_EUNSUPPORTED;
-    return resolve_plan(is_msv ? 1 : 0, M, db->table_rows, nullptr, plan);
+    return resolve_plan(is_msv ? 1 : 0, M, db->table_rows, Range{db->cum_rows.data(), db->nseq},
+                        nullptr, plan);
 }
 
 hmsv_status hmsv_default_plan(int32_t is_msv, int32_t M, hmsv_plan *plan) {
@@ -811,7 +940,8 @@ hmsv_status hmsv_default_plan(int32_t is_msv, int32_t M, hmsv_plan *plan) {
     // The autotuned plan (paper Sec. 3.4 picks its kernel per model length
     // the same way): among the tuned M-bins of this filter, nearest to M in
     // log distance first (ties to the smaller bin), the first whose group
-    // width still holds the profile within Q <= 32 registers and the LDS.
+    // width still holds the profile (a kernel has its registers per lane) and
+    // the LDS.
     int idx[kNumTuned];
     int n = 0;
     for (int i = 0; i < kNumTuned; ++i)
@@ -829,7 +959,7 @@ hmsv_status hmsv_default_plan(int32_t is_msv, int32_t M, hmsv_plan *plan) {
         const TunedPlan &tp = kTuned[idx[t]];
         int G = tp.G;
         int Q = (M + 1 + 2 * G - 1) / (2 * G);
-        if (Q > 32 || lds_bytes(G, Q) > (size_t)kLdsBytes) continue;
+        if (lds_bytes(G, Q) > (size_t)kLdsBytes) continue;
         if (!registry().find(is_msv ? 1 : 0, G, Q)) continue;
         plan->G = G;
         plan->Q = Q;
@@ -837,11 +967,10 @@ hmsv_status hmsv_default_plan(int32_t is_msv, int32_t M, hmsv_plan *plan) {
         plan->blocks = 0;
         return HMSV_OK;
     }
-    // Untuned fallback: the narrowest lane group whose registers (Q <= 32
-    // per lane) still hold the profile.
+    // Untuned fallback: the narrowest lane group that holds the profile.
     for (int G : {1, 2, 4, 8, 16, 32, 64}) {
         int Q = (M + 1 + 2 * G - 1) / (2 * G);
-        if (Q > 32 || lds_bytes(G, Q) > (size_t)kLdsBytes) continue;
+        if (lds_bytes(G, Q) > (size_t)kLdsBytes) continue;
         if (!registry().find(is_msv ? 1 : 0, G, Q)) continue;
         plan->G = G;
         plan->Q = Q;
@@ -906,19 +1035,22 @@ hmsv_status hmsv_split_info(const hmsv_db *db, int64_t first, int64_t count, int
     if (!db || !nsplit || !nsegs || !seg_rows) return HMSV_EINVAL;
     if (M < 1) return HMSV_EINVAL;
     if (M > HMSV_MAX_M) return HMSV_EUNSUPPORTED;
+    if (count == -1 && first == 0) count = db->nseq;
+    const bool in_range = first >= 0 && count >= 0 && first <= db->nseq && count <= db->nseq - first;
     hmsv_plan plan;
-    hmsv_status st = resolve_plan(is_msv ? 1 : 0, M, db->table_rows, plan_in, &plan);
+    hmsv_status st = resolve_plan(
+        is_msv ? 1 : 0, M, db->table_rows,
+        Range{db->cum_rows.data() + (in_range ? first : 0), in_range ? count : 0}, plan_in, &plan);
     if (st != HMSV_OK) return st;
     const KernelEntry *e = registry().find(is_msv ? 1 : 0, plan.G, plan.Q);
     if (!e) return HMSV_ENOKERNEL;
-    if (count == -1 && first == 0) count = db->nseq;
-    if (first < 0 || count < 0 || first > db->nseq || count > db->nseq - first) return HMSV_EINVAL;
+    if (!in_range) return HMSV_EINVAL;
     *nsplit = *nsegs = *seg_rows = 0;
     if (count == 0) return HMSV_OK;
-    const int blocks = grid_blocks(e, plan, count, db->table_rows);
+    int blocks = grid_blocks(e, plan, count, db->table_rows);
     if (blocks <= 0) return HMSV_EDEVICE;
     KArgs a{};
-    plan_split(db, first, count, (int64_t)blocks * plan.waves_per_block * (64 / plan.G), M, a);
+    plan_split(db, first, count, e, plan, M, &blocks, a);
     *nsplit = a.nsplit;
     *nsegs = a.nsegs;
     *seg_rows = a.seg_rows;
@@ -1169,6 +1301,7 @@ hmsv_status hmsv_batch_create(const hmsv_query *queries, int32_t nq, const hmsv_
         for (int k = 0; k < i; ++k)
             if (queries[k].workspace == q.workspace) return HMSV_EINVAL;
         st = resolve_plan(q.is_msv ? 1 : 0, q.prof.M, db->table_rows,
+                          Range{db->cum_rows.data(), db->nseq},
                           q.plan.G == 0 ? nullptr : &q.plan, &plans[i]);
         if (st != HMSV_OK) return st;
         if (!registry().find(q.is_msv ? 1 : 0, plans[i].G, plans[i].Q)) return HMSV_ENOKERNEL;

@@ -34,7 +34,8 @@ def _same(hm, filt, emis, res, off, plan):
     prof = hm.Profile.from_emissions(emis, synth.BG)
     gdb = hm.Database(res, off)
     n = len(off) - 1
-    s = torch.full((n,), 99, dtype=torch.uint8, device="cuda")
+    sdt = torch.uint8 if filt == "msv" else torch.int8
+    s = torch.full((n,), 99, dtype=sdt, device="cuda")
     f = torch.full((n,), 99, dtype=torch.uint8, device="cuda")
     (hm.msv_score if filt == "msv" else hm.ssv_score)(prof, gdb, s, f, plan=plan)
     torch.cuda.synchronize()
