@@ -25,7 +25,8 @@ M_BINS = (30, 40, 48, 64, 80, 96, 120, 128, 160, 192, 240, 256, 320, 400, 480, 5
           896, 1000, 1024, 1280, 1536, 1920, 2048, 2400, 3072, 3839)
 GROUPS = (1, 2, 4, 8, 16, 32, 64)
 WAVES = (2, 3, 4, 5, 6, 8)
-QMAX = 32
+# registers per lane the kernels are built for, per group width
+QMAX = {1: 32, 2: 64, 4: 64, 8: 64, 16: 64, 32: 60, 64: 30}
 LDS_LIMIT = 160 * 1024
 
 
@@ -42,9 +43,9 @@ def q_for(G, M):
 def candidates(filt, M):
     for G in GROUPS:
         Q = q_for(G, M)
-        if Q > QMAX or lds_bytes(G, Q) > LDS_LIMIT:
+        if Q > QMAX[G] or lds_bytes(G, Q) > LDS_LIMIT:
             continue
-        for wpb in WAVES + ((12, 16) if G >= 32 else ()):
+        for wpb in WAVES + ((12, 16) if G >= 32 or Q > 32 else ()):
             yield (G, Q, wpb, 0)
 
 
@@ -74,7 +75,7 @@ def lookup(table, key, filt, M):
     for b in sorted(bins, key=lambda b: abs(math.log(b) - math.log(M))):
         G, _, wpb, blocks = ent[str(b)]
         Q = q_for(G, M)
-        if Q <= QMAX and lds_bytes(G, Q) <= LDS_LIMIT:
+        if Q <= QMAX[G] and lds_bytes(G, Q) <= LDS_LIMIT:
             return (G, Q, wpb, blocks)
     return None
 

@@ -34,7 +34,7 @@ COMMON = ["-O3", f"--offload-arch={ARCH}", "-std=c++20", "-fPIC",
 
 # (G, largest Q).  The LDS table is 21 rows x G x Q dwords and must fit in
 # 160 KiB, which caps G = 64 at Q = 30 (profiles up to 3840 nodes).
-GROUPS = ((1, 32), (2, 32), (4, 32), (8, 32), (16, 32), (32, 32), (64, 30))
+GROUPS = ((1, 32), (2, 64), (4, 64), (8, 64), (16, 64), (32, 60), (64, 30))
 QCHUNK = 4
 # P7Viterbi kernels: (G, largest Q); 28 table rows cap G = 64 at Q = 22.
 P7_GROUPS = ((4, 16), (8, 16), (16, 16), (32, 16), (64, 22))

@@ -175,6 +175,11 @@ __device__ __forceinline__ uint32_t slot_bits(const KArgs &a, int x, int s) {
     return (uint32_t)__builtin_bit_cast(unsigned short, h);
 }
 
+// Ring of score chunks of the lanes with more than kRingQ registers, which
+// read scores kRing - 1 chunks of four ahead instead of whole rows.
+constexpr int kRing = 4;
+constexpr int kRingQ = 32;
+
 template <int G, int Q, bool MSV>
 struct Lane {
     using Lay = Layout<G, Q>;
@@ -230,8 +235,7 @@ struct Lane {
         update(c);
     }
 
-    // The cell update of one row, given the row's scores: in place, registers
-    // in descending order (register q takes the old q - 1).
+    // The cell update of one row, given the row's scores.
     __device__ __forceinline__ void update(const uint32_t (&c)[Q]) {
         uint32_t gam = shift_in(R[Q - 1]);
         uint32_t prev_v = 0;
@@ -245,6 +249,47 @@ struct Lane {
             gam = old;
         }
         if (Q & 1) xE = hmax(xE, prev_v);
+    }
+
+    // The chunk (4 registers) ch of row x's scores.
+    static constexpr int NCH = (Q + 3) / 4;
+    __device__ __forceinline__ void load_chunk(const uint32_t *TW, uint32_t x, int ch,
+                                               uint32_t (&c)[4]) {
+        const uint4 v = *(const uint4 *)((const char *)TW + x * (uint32_t)(RS * 4) +
+                                         ch * Lay::CW * 4);
+        c[0] = v.x; c[1] = v.y; c[2] = v.z; c[3] = v.w;
+    }
+
+    // One row, in place, registers in descending order (register q takes the
+    // old q - 1), its scores read kRing - 1 chunks ahead: buf holds the row's first kRing - 1 (its last chunks),
+    // in ring slots SLOT0, SLOT0 + 1, ...; the turns of the rest read the first
+    // ones of the next row (residue xn).
+    template <int SLOT0>
+    __device__ __forceinline__ void row_ahead(const uint32_t *TW, uint32_t x, uint32_t xn,
+                                              uint32_t (&buf)[kRing][4]) {
+        const uint32_t gam = shift_in(R[Q - 1]);
+        uint32_t pend = 0;
+        [&]<int... C>(std::integer_sequence<int, C...>) {
+            (([&] {
+                 constexpr int ahead = C + kRing - 1;
+                 constexpr int dst = (SLOT0 + ahead) % kRing;
+                 if constexpr (ahead < NCH) load_chunk(TW, x, NCH - 1 - ahead, buf[dst]);
+                 else load_chunk(TW, xn, 2 * NCH - 1 - ahead, buf[dst]);
+#pragma unroll
+                 for (int u = 3; u >= 0; --u) {
+                     const int q = (NCH - 1 - C) * 4 + u;
+                     if (q >= Q) continue;
+                     R[q] = add_clamp(q > 0 ? R[q > 0 ? q - 1 : 0] : gam,
+                                      buf[(SLOT0 + C) % kRing][u]);
+                     if ((Q - 1 - q) & 1) xE = hmax3(xE, pend, R[q]);
+                     else pend = R[q];
+                 }
+                 // keeps the scheduler from hoisting later chunks' loads
+                 __builtin_amdgcn_sched_barrier(0);
+             }()),
+             ...);
+        }(std::make_integer_sequence<int, NCH>{});
+        if (Q & 1) xE = hmax(xE, pend);
     }
 };
 
@@ -559,6 +604,15 @@ filter_kernel(KArgs a) {
         uint32_t ca[PIPE ? Q : 1], cb[PIPE ? Q : 1];
         auto xrow = [&](int r) -> uint32_t { return (wv[r / 4] >> (8 * (r % 4))) & 0xffu; };
         if constexpr (PIPE) st.load_row(T[0], T[1], T[2], xrow(0), ca);
+        constexpr bool RING = Q > kRingQ;
+        static_assert(!RING || (!Lay::T2 && !Lay::T1), "rings hold whole chunks");
+        static_assert(!RING || (16 * L::NCH) % kRing == 0, "a step leaves the ring where it was");
+        uint32_t ring[RING ? kRing : 1][4];
+        if constexpr (RING) {
+#pragma unroll
+            for (int ch = 0; ch < kRing - 1; ++ch)
+                st.load_chunk(T[0], xrow(0), L::NCH - 1 - ch, ring[ch]);
+        }
         do {
             const uint32_t offn = next_off(off);
             uint32_t wn[K];
@@ -578,6 +632,15 @@ filter_kernel(KArgs a) {
                         st.load_row(T[0], T[1], T[2], wn[0] & 0xffu, nxt);
                     }
                     st.update(cur);
+                } else if constexpr (RING) {
+                    if constexpr (r + 1 < 4 * K) {
+                        st.template row_ahead<(r * L::NCH) % kRing>(T[0], xrow(r), xrow(r + 1), ring);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < K; ++k) asm volatile("" : "+v"(wn[k]));
+                        st.template row_ahead<(r * L::NCH) % kRing>(T[0], xrow(r), wn[0] & 0xffu,
+                                                                    ring);
+                    }
                 } else {
                     st.row(T, xrow(r));
                 }
@@ -657,7 +720,7 @@ filter_kernel(KArgs a) {
                     x[3] = glast;
                 } else {
                     msv_settle(a, id, mx, gfirst, glast, seq_off, seq_end,
-                               (uint32_t)(tjbm - a.tbm));
+                                  (uint32_t)(tjbm - a.tbm));
                 }
             }
             need = ended;
@@ -1036,6 +1099,8 @@ __global__ void __launch_bounds__(THREADS) exact_kernel(KArgs a) {
 // the compiler budgets registers for the block size it is told.
 template <int G>
 constexpr int kMaxWaves = G >= 32 ? 16 : 8;
+template <int G, int Q>
+constexpr int kMaxWavesQ = (G >= 32 || Q > 32) ? 16 : 8;
 
 template <int G, int Q, int MODE, int THREADS>
 hipError_t launch_filter_kernel(const KArgs &a, int wpb, int blocks, hipStream_t s) {
@@ -1052,7 +1117,7 @@ hipError_t launch_filter_kernel(const KArgs &a, int wpb, int blocks, hipStream_t
 
 template <int G, int Q, int MODE>
 hipError_t launch_filter_mode(const KArgs &a, int wpb, int blocks, hipStream_t s) {
-    if constexpr (kMaxWaves<G> > 8) {
+    if constexpr (kMaxWavesQ<G, Q> > 8) {
         if (wpb > 8) return launch_filter_kernel<G, Q, MODE, 1024>(a, wpb, blocks, s);
     }
     return launch_filter_kernel<G, Q, MODE, 512>(a, wpb, blocks, s);
@@ -1066,7 +1131,7 @@ hipError_t launch_filter(const KArgs &a, int wpb, int blocks, hipStream_t s) {
     if (a.rows != kRows && a.rows != kDegenRows) return hipErrorInvalidValue;
     const int n = a.rows * Layout<G, Q>::RS;
     const int nb = (n + 255) / 256;
-    if (wpb < 1 || wpb > kMaxWaves<G>) return hipErrorInvalidValue;
+    if (wpb < 1 || wpb > kMaxWavesQ<G, Q>) return hipErrorInvalidValue;
     const int xb = MSV ? (a.rows * lds_layout(kExactG, a.qx).RS + 255) / 256 : 0;
     const int seg_blocks = (a.nsegs + 255) / 256;
     hipLaunchKernelGGL((prep_kernel<G, Q, MSV>), dim3(nb + xb + (MSV ? a.rows : 0) + seg_blocks),
@@ -1104,8 +1169,8 @@ int occupancy_kernel(int wpb, int rows) {
 template <int G, int Q, bool MSV>
 int occupancy_filter(int wpb, int rows) {
     constexpr int MODE = MSV ? kMSV : kSSV;
-    if (wpb < 1 || wpb > kMaxWaves<G>) return 0;
-    if constexpr (kMaxWaves<G> > 8) {
+    if (wpb < 1 || wpb > kMaxWavesQ<G, Q>) return 0;
+    if constexpr (kMaxWavesQ<G, Q> > 8) {
         if (wpb > 8) return occupancy_kernel<G, Q, MODE, 1024>(wpb, rows);
     }
     return occupancy_kernel<G, Q, MODE, 512>(wpb, rows);
