@@ -136,33 +136,59 @@ __global__ void __launch_bounds__(THREADS) p7_fast_kernel(P7Args a) {
         load_all(rT + kFDD, tDD);
     }
 
-    P7Queue<G> queue(a.fqueue, lane, j);
+    // Records run longest first.  A group starts on the record of its own
+    // number; wavefronts are numbered across the blocks before within them, so
+    // the longest records spread over the CUs.  Later records are claimed when
+    // the current one has at most 48 rows left, in three steps of 16: the claim,
+    // its value and the record's load, the last rows.  (Claimed a record or two
+    // ahead, as the filter kernels do, a long record holds back what was claimed
+    // behind it, and P7's rows are long enough to hide the claim.)
     const int32_t *sel = a.sel;
     const int nseq = sel ? min(max(*a.nsel, 0), a.nseq) : a.nseq;
-    auto take = [&]() -> int { return queue.take(sel, nseq); };
+    const int wave = (int)(threadIdx.x >> 6) * (int)gridDim.x + (int)blockIdx.x;
+    const int gid = wave * (64 / G) + lane / G;
+    const int ngroups = (int)(gridDim.x * (blockDim.x >> 6)) * (64 / G);
+    const int nparts = (int)(gridDim.x < (unsigned)kP7Parts ? gridDim.x : (unsigned)kP7Parts);
+    const int part = (int)(blockIdx.x % (unsigned)nparts);
+    uint32_t *ctr = a.fqueue + part * 32;
+    // claims of the wavefront's last issue: lane 0 holds the counter's value, a
+    // claiming group's first lane its rank among them
+    uint32_t cbase = 0u, crank = 0u;
+    auto issue = [&](bool want) {
+        const bool w = want && gstart;
+        const unsigned long long m = __ballot(w);
+        if (lane == 0) cbase = atomicAdd(ctr, (uint32_t)__popcll(m));
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (w) crank = rank;
+    };
+    // the claimed processing position, or -1: none left
+    auto position = [&](long long r) -> int {
+        if (r >= (long long)nseq) return -1;
+        return sel ? sel[r] : (int)r;
+    };
+    auto take = [&]() -> int {
+        int k = (int)crank;
+        if constexpr (G > 1) k = __shfl(k, lane - j);
+        k += __builtin_amdgcn_readfirstlane((int)cbase);
+        return position((long long)ngroups + (long long)part + (long long)nparts * (long long)k);
+    };
 
     uint32_t M[Q], I[Q], D[Q];
-    queue.issue(true);
-    int t = take();
+    int t = position(gid), tn = -1;
     uint4 rec = make_uint4(0u, 0u, 0u, 0u), rec16 = rec;
     uint32_t lm = 0u;
-    if (t >= 0) {
-        rec = *(const uint4 *)(a.seqs + t);
-        rec16 = *((const uint4 *)(a.seqs + t) + 1);
-        lm = a.lenmodel[t];
-    }
-    // the next record, claimed and loaded while the current one runs
-    queue.issue(true);
-    int tn = take();
-    uint4 nrec = rec, nrec16 = rec16;
-    uint32_t nlm = lm;
-    auto prefetch = [&]() {
-        if (tn >= 0) {
-            nrec = *(const uint4 *)(a.seqs + tn);
-            nrec16 = *((const uint4 *)(a.seqs + tn) + 1);
-            nlm = a.lenmodel[tn];
+    auto load_record = [&](int p, uint4 &r, uint4 &r16, uint32_t &l) {
+        if (p >= 0) {
+            r = *(const uint4 *)(a.seqs + p);
+            r16 = *((const uint4 *)(a.seqs + p) + 1);
+            l = a.lenmodel[p];
         }
     };
+    load_record(t, rec, rec16, lm);
+    uint4 nrec = rec, nrec16 = rec16;
+    uint32_t nlm = lm;
+    int claim = 0;               // 0: none, 1: issued, 2: tn and its record loaded
 
     bool active = false, ovf = false, give_up = false;
     uint32_t off = a.pad_off, id = 0;
@@ -202,13 +228,29 @@ __global__ void __launch_bounds__(THREADS) p7_fast_kernel(P7Args a) {
         }
     };
     start();
-    prefetch();
-    queue.issue(true);           // the record after that, taken at the switch
 
     for (;;) {
         if (!__any(active)) break;
         bool ended = false;
         do {
+            // the next record (see above)
+            const bool late = active && len - done <= 48;
+            if (__any(late)) {
+                const bool ready = claim == 1;
+                if (__any(ready)) {
+                    const int p = take();
+                    if (ready) {
+                        tn = p;
+                        load_record(tn, nrec, nrec16, nlm);
+                        claim = 2;
+                    }
+                }
+                const bool want = late && claim == 0;
+                if (__any(want)) {
+                    issue(want);
+                    if (want) claim = 1;
+                }
+            }
             // residues of the next step (the database stores every sequence
             // in whole 16-residue steps plus 16 more bytes)
             const uint4 wn = *(const uint4 *)(a.res + off + 16u);
@@ -436,17 +478,21 @@ __global__ void __launch_bounds__(THREADS) p7_fast_kernel(P7Args a) {
                 }
             }
         }
-        const int claimed = take();
+        if (__any(ended && claim == 1)) {        // records of at most 16 rows
+            const int p = take();
+            if (ended && claim == 1) {
+                tn = p;
+                load_record(tn, nrec, nrec16, nlm);
+            }
+        }
         if (ended) {
             t = tn;
-            tn = claimed;
             rec = nrec;
             rec16 = nrec16;
             lm = nlm;
+            claim = 0;
             start();
-            prefetch();
         }
-        queue.issue(ended);
     }
 }
 
