@@ -293,6 +293,16 @@ struct Lane {
     }
 };
 
+// A wavefront's number in its grid: four of each block (one per SIMD of its
+// CU), then the next four of each, and so on.  Lane groups of lower numbers
+// take longer records, so each SIMD of a CU gets some of each length.
+__device__ __forceinline__ int wave_rank() {
+    const int w = (int)(threadIdx.x >> 6), per_block = (int)(blockDim.x >> 6);
+    const int four = w & ~3;
+    const int n = per_block - four < 4 ? per_block - four : 4;
+    return four * (int)gridDim.x + (int)blockIdx.x * n + (w & 3);
+}
+
 // Kernel modes.  MSV runs as two launches: filter_kernel in mode kMSV
 // scores every sequence with scB fixed and settles all but the few whose
 // running max passes base + tec (where the J state may open); for those it
@@ -408,7 +418,7 @@ filter_kernel(KArgs a) {
     const int nsplit = a.nsplit;
     const int nv = nsegs + a.nseq - nsplit;       // ranges are never empty
     const int ngroups = (int)(gridDim.x * (blockDim.x / G));
-    const int gid = (int)(blockIdx.x * (blockDim.x / G) + threadIdx.x / G);
+    const int gid = wave_rank() * (64 / G) + (int)(threadIdx.x & 63) / G;
 
     L st;
     uint32_t off = a.pad_off;

@@ -137,16 +137,14 @@ __global__ void __launch_bounds__(THREADS) p7_fast_kernel(P7Args a) {
     }
 
     // Records run longest first.  A group starts on the record of its own
-    // number; wavefronts are numbered across the blocks before within them, so
-    // the longest records spread over the CUs.  Later records are claimed when
+    // number (see wave_rank).  Later records are claimed when
     // the current one has at most 48 rows left, in three steps of 16: the claim,
     // its value and the record's load, the last rows.  (Claimed a record or two
     // ahead, as the filter kernels do, a long record holds back what was claimed
     // behind it, and P7's rows are long enough to hide the claim.)
     const int32_t *sel = a.sel;
     const int nseq = sel ? min(max(*a.nsel, 0), a.nseq) : a.nseq;
-    const int wave = (int)(threadIdx.x >> 6) * (int)gridDim.x + (int)blockIdx.x;
-    const int gid = wave * (64 / G) + lane / G;
+    const int gid = wave_rank() * (64 / G) + lane / G;
     const int ngroups = (int)(gridDim.x * (blockDim.x >> 6)) * (64 / G);
     const int nparts = (int)(gridDim.x < (unsigned)kP7Parts ? gridDim.x : (unsigned)kP7Parts);
     const int part = (int)(blockIdx.x % (unsigned)nparts);
