@@ -210,7 +210,7 @@ int32_t hmsv_db_table_rows(const hmsv_db *db);
  * cells, so the group covers 2*G*Q - 1 >= M nodes (one cell is a fixed
  * -inf node).  64/G sequences share a wavefront (the paper's
  * multi-sequence alignment, Sec. 3.1 tier 4).  waves_per_block (1..8, or
- * 1..16 for G >= 32) wavefronts share one LDS copy of the profile;
+ * 1..16 for G >= 32 or Q > 32) wavefronts share one LDS copy of the profile;
  * blocks = 0 picks a persistent grid of the resident maximum. */
 typedef struct {
     int32_t G;
@@ -224,8 +224,8 @@ typedef struct {
  * table of the plans measured fastest on MI355X (gfx950, 256 CUs) per
  * filter and profile-length bin is compiled in; the bin nearest to M in
  * log distance (ties to the smaller bin) whose group width G holds the
- * profile in Q <= 32 registers per lane gives G and waves_per_block, and
- * Q = ceil((M + 1) / 2G).  Lengths no tuned width can hold fall back to the
+ * profile (Q <= 32 registers per lane at G = 1, 64 at 2..16, 60 at 32, 30 at
+ * 64) gives G and waves_per_block, and Q = ceil((M + 1) / 2G).  Lengths no tuned width can hold fall back to the
  * narrowest group that can.  Host only; no device is queried.  Fails with
  * HMSV_EINVAL on a null plan or M < 1, HMSV_EUNSUPPORTED for
  * M > HMSV_MAX_M. */
@@ -239,18 +239,21 @@ hmsv_status hmsv_default_plan(int32_t is_msv, int32_t M, hmsv_plan *plan);
  * database that holds degenerate codes it has 27 rows (x 27 / 21). */
 size_t hmsv_plan_lds_bytes(int32_t G, int32_t Q);
 
-/* The plan a call with plan = NULL uses on this database: hmsv_default_plan,
- * or, when the database holds degenerate codes and that plan's 27-row image
- * does not fit the LDS, the narrowest lane group whose image does (LDS
- * bytes are then hmsv_plan_lds_bytes x 27 / 21).  HMSV_EUNSUPPORTED if none
- * does (or, for MSV, if the exact pass's 64-lane image does not). */
+/* The plan a call with plan = NULL uses on this database: the group width
+ * whose time, estimated from the lengths of the database's sequences and M,
+ * is least.  Large databases run hmsv_default_plan's (measured on 500,000
+ * sequences) unless another is expected to be 5% faster; small ones run
+ * wider groups.  Only widths whose image fits the LDS are taken (with
+ * degenerate codes it has 27 rows: hmsv_plan_lds_bytes x 27 / 21).  A range
+ * call with plan = NULL chooses for its range.  HMSV_EUNSUPPORTED if the
+ * 64-lane image of the profile does not fit. */
 hmsv_status hmsv_db_default_plan(const hmsv_db *db, int32_t is_msv, int32_t M, hmsv_plan *plan);
 
 /* Device workspace needed by a scoring call on a database of nseq
  * sequences (bytes; pass the database's full sequence count, also for
  * range calls): the work-queue counters, the MSV per-residue best scores,
  * the profile converted to the kernel's LDS layout, the records of split
- * sequences' segments (at most 131072 segments of 65536 sequences per
+ * sequences' segments (at most 131008 segments of 65536 sequences per
  * call; about 8.7 MB), and 16 bytes per sequence for the MSV rescoring
  * windows. */
 size_t hmsv_workspace_bytes(int64_t nseq);
@@ -347,7 +350,8 @@ hmsv_status hmsv_db_order(const hmsv_db *db, int64_t *ids);
  * the same plan.
  * Each query owns its outputs and workspace (device, caller-owned, distinct
  * per query); score is uint8 for MSV, int8 for SSV.  plan.G == 0 selects
- * the library's default (autotuned) plan.  The batch keeps pointers, not copies, of
+ * the library's choice for queries that share the GPU (hmsv_batch_plan
+ * tells which).  The batch keeps pointers, not copies, of
  * the device buffers; the profile struct is copied.  branches: 1..16.
  * Fails with HMSV_EINVAL on bad arguments (including a workspace shared by
  * two queries), the errors of hmsv_*_score for a query, HMSV_EDEVICE if
@@ -365,6 +369,8 @@ typedef struct hmsv_batch hmsv_batch;
 hmsv_status hmsv_batch_create(const hmsv_query *queries, int32_t nq, const hmsv_db *db,
                               int32_t branches, hmsv_batch **out);
 hmsv_status hmsv_batch_launch(hmsv_batch *batch, hipStream_t stream);
+/* The plan of query i (plan.G == 0 resolved). */
+hmsv_status hmsv_batch_plan(const hmsv_batch *batch, int32_t i, hmsv_plan *plan);
 void hmsv_batch_destroy(hmsv_batch *batch);
 
 /* ---- P7Viterbi: the gapped Plan-7 Viterbi filter ------------------------
@@ -429,8 +435,10 @@ hmsv_status hmsv_p7_default_plan(int32_t M, hmsv_plan *plan);
  * saturation (score 32767), both device arrays of nseq entries in the
  * caller's original order.  workspace: hmsv_workspace_bytes(nseq) bytes,
  * 256-byte aligned (calls sharing it must be ordered on one stream).  plan:
- * NULL for the default (plans take 1..8 waves per block, 1..16 for
- * 64-lane groups of at most 18 registers or of 20).  Lane groups take
+ * NULL for the width of the least expected time on this database (large
+ * ones: hmsv_p7_default_plan's or near it; small ones: wider groups; plans
+ * take 1..8 waves per block, 1..16 for 64-lane groups of at most 18 registers
+ * or of 20).  Lane groups take
  * the records (longest first) from a queue in the workspace as they finish
  * one; each sequence runs exactly its L rows.  score and flags may be
  * NULL for a database without sequences.

@@ -150,7 +150,7 @@ EXPORTED = ("hmsv_strerror", "hmsv_tbm", "hmsv_tjb", "hmsv_quantize", "hmsv_db_c
             "hmsv_db_destroy", "hmsv_db_nseq", "hmsv_db_residues", "hmsv_db_padded_rows",
             "hmsv_default_plan", "hmsv_plan_lds_bytes", "hmsv_workspace_bytes",
             "hmsv_msv_score", "hmsv_ssv_score",
-            "hmsv_batch_create", "hmsv_batch_launch", "hmsv_batch_destroy",
+            "hmsv_batch_create", "hmsv_batch_launch", "hmsv_batch_plan", "hmsv_batch_destroy",
             "hmsv_msv_score_range", "hmsv_ssv_score_range", "hmsv_db_order",
             "hmsv_split_info", "hmsv_score_nats", "hmsv_gumbel_pvalue",
             "hmsv_msv_score_noalloc", "hmsv_db_table_rows", "hmsv_db_default_plan",

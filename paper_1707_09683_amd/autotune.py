@@ -86,18 +86,20 @@ HEADER = os.path.join(HERE, "csrc", "tuned_plans.inc")
 
 def emit_header(table=None, key=DEVICE_KEY) -> str:
     """C table of the tuned plans for ``key``: {is_msv, M-bin, G, waves per
-    block}, read by hmsv_default_plan."""
+    block}, read by hmsv_default_plan; then those of ``key:batch`` (plans of at
+    most 32 registers per lane), is_msv + 2."""
     table = load_table() if table is None else table
     rows = []
-    for filt in ("msv", "ssv"):
-        for b, (G, _Q, wpb, blocks) in sorted(((int(k), v) for k, v in
-                                               table.get(key, {}).get(filt, {}).items())):
-            if blocks != 0:
-                raise ValueError("tuned plans use persistent grids (blocks = 0)")
-            rows.append(f"    {{{1 if filt == 'msv' else 0}, {b}, {G}, {wpb}}},")
+    for sub, add in ((key, 0), (key + ":batch", 2)):
+        for filt in ("msv", "ssv"):
+            for b, (G, _Q, wpb, blocks) in sorted(((int(k), v) for k, v in
+                                                   table.get(sub, {}).get(filt, {}).items())):
+                if blocks != 0:
+                    raise ValueError("tuned plans use persistent grids (blocks = 0)")
+                rows.append(f"    {{{add + (1 if filt == 'msv' else 0)}, {b}, {G}, {wpb}}},")
     return ("// Tuned launch plans for " + key + " (MI355X), generated from tuned_plans.json\n"
             "// by paper_1707_09683_amd/autotune.py emit_header(); regenerated by the build.\n"
-            "// {is_msv, M-bin, G, waves per block}; Q follows from G and M.\n"
+            "// {is_msv (+ 2: for batches), M-bin, G, waves per block}; Q follows from G and M.\n"
             + "\n".join(rows) + "\n")
 
 

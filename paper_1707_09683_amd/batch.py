@@ -11,8 +11,7 @@ import ctypes
 
 import torch
 
-from . import (_CProfile, Plan, Profile, Database, _lib, _check, workspace_bytes,
-               db_default_plan)
+from . import (_CProfile, Plan, Profile, Database, _lib, _check, workspace_bytes)
 
 
 class _CQuery(ctypes.Structure):
@@ -26,6 +25,8 @@ _lib.hmsv_batch_create.argtypes = [ctypes.POINTER(_CQuery), ctypes.c_int32, ctyp
                                    ctypes.c_int32, ctypes.POINTER(ctypes.c_void_p)]
 _lib.hmsv_batch_launch.restype = ctypes.c_int
 _lib.hmsv_batch_launch.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+_lib.hmsv_batch_plan.restype = ctypes.c_int
+_lib.hmsv_batch_plan.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(Plan)]
 _lib.hmsv_batch_destroy.restype = None
 _lib.hmsv_batch_destroy.argtypes = [ctypes.c_void_p]
 
@@ -33,7 +34,7 @@ _lib.hmsv_batch_destroy.argtypes = [ctypes.c_void_p]
 class Batch:
     """``queries``: list of (filter, Profile) with filter "msv" or "ssv".
 
-    ``plans``: optional list of Plan (None entries = tuned/default plan).
+    ``plans``: optional list of Plan (None entries = the library's choice).
     After ``launch()`` and a stream sync, ``scores[i]`` / ``flags[i]`` hold
     query i's results in the database's original sequence order."""
 
@@ -55,24 +56,26 @@ class Batch:
             s = torch.empty(n, dtype=sdt, device=dev)
             f = torch.empty(n, dtype=torch.uint8, device=dev)
             ws = torch.zeros(workspace_bytes(n), dtype=torch.uint8, device=dev)
-            p = plans[i] if plans is not None and plans[i] is not None \
-                else db_default_plan(db, filt, prof.M)
+            p = plans[i] if plans is not None and plans[i] is not None else Plan()
             self.scores.append(s)
             self.flags.append(f)
             self.workspaces.append(ws)
-            self.plans.append(p)
             arr[i].is_msv = 1 if filt == "msv" else 0
             arr[i].prof = prof._c
             arr[i].score = s.data_ptr()
             arr[i].flags = f.data_ptr()
             arr[i].workspace = ws.data_ptr()
-            arr[i].plan = p if p is not None else Plan()
+            arr[i].plan = p
         self._arr = arr
         h = ctypes.c_void_p()
         with torch.cuda.device(dev):
             _check(_lib.hmsv_batch_create(arr, len(queries), db._h, int(branches),
                                           ctypes.byref(h)), "hmsv_batch_create")
         self._h = h
+        for i in range(len(queries)):
+            p = Plan()
+            _check(_lib.hmsv_batch_plan(h, i, ctypes.byref(p)), "hmsv_batch_plan")
+            self.plans.append(p)
         self.device = dev
 
     def launch(self, stream=None):

@@ -21,6 +21,7 @@ struct hmsv_batch {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     int nq = 0;
+    std::vector<hmsv_plan> plans;     // as captured
 };
 
 struct hmsv_db {
@@ -130,7 +131,8 @@ Registry &registry() {
 }
 
 // Launch plans the autotuner measured fastest on MI355X (gfx950, 256 CUs)
-// per filter and profile-length bin, compiled in from tuned_plans.json.
+// per filter (is_msv; + 2: for batches) and profile-length bin, compiled in from
+// tuned_plans.json.
 struct TunedPlan { int is_msv; int bin; int G; int waves_per_block; };
 const TunedPlan kTuned[] = {
 #include "tuned_plans.inc"
@@ -208,6 +210,41 @@ hmsv_status check_plan(const hmsv_plan *pl, int M, int rows = kRows) {
     return HMSV_OK;
 }
 
+// kind: kTuned's is_msv.
+bool tuned_plan(int kind, int M, hmsv_plan *plan) {
+    // The autotuned plan (paper Sec. 3.4 picks its kernel per model length
+    // the same way): among the tuned M-bins of this filter, nearest to M in
+    // log distance first (ties to the smaller bin), the first whose group
+    // width still holds the profile (a kernel has its registers per lane) and
+    // the LDS.
+    int idx[kNumTuned];
+    int n = 0;
+    for (int i = 0; i < kNumTuned; ++i)
+        if (kTuned[i].is_msv == kind) idx[n++] = i;
+    auto dist = [M](int b) { return std::fabs(std::log((double)b) - std::log((double)M)); };
+    auto before = [&](int a, int b) {
+        double da = dist(kTuned[a].bin), db = dist(kTuned[b].bin);
+        if (da != db) return da < db;
+        return kTuned[a].bin < kTuned[b].bin;
+    };
+    // insertion sort of the few bins (stable, and allocates nothing)
+    for (int t = 1; t < n; ++t)
+        for (int u = t; u > 0 && before(idx[u], idx[u - 1]); --u) std::swap(idx[u], idx[u - 1]);
+    for (int t = 0; t < n; ++t) {
+        const TunedPlan &tp = kTuned[idx[t]];
+        int G = tp.G;
+        int Q = (M + 1 + 2 * G - 1) / (2 * G);
+        if (lds_bytes(G, Q) > (size_t)kLdsBytes || (kind >= 2 && Q > 32)) continue;
+        if (!registry().find(kind & 1, G, Q)) continue;
+        plan->G = G;
+        plan->Q = Q;
+        plan->waves_per_block = tp.waves_per_block;
+        plan->blocks = 0;
+        return true;
+    }
+    return false;
+}
+
 // ---- what a call's rows cost ------------------------------------------------
 // A model of the filter kernel's time, in shader cycles, for choosing how a
 // call is cut and how wide its lane groups are.  Its figures are a fit to 2,850
@@ -266,12 +303,17 @@ constexpr double kCutCycles = 9000.0, kSegCycles = 2.5;
 // done: records above the mean work per group (total rows / lane groups) are
 // cut, down to the length at which the rows that segments repeat (warm =
 // M - 1 rounded up to 16 before each) cost more than the wait they save.
-Cut choose_cut(const Range &r, int M, int G, int Q, int64_t ngroups) {
+// share: calls of this size that run at the same time (queries of a batch),
+// taken as so many times the records: one's end is filled by the others
+// (1500 nodes and four shorter profiles on 20,000 sequences at once, cut as if
+// alone 817 us, so 737; eight of up to 1800 on 60,000 2770 and 2711).
+Cut choose_cut(const Range &r, int M, int G, int Q, int64_t ngroups, int share = 1) {
     const int64_t warm = ((M - 1) + 15) & ~15;
-    const int64_t total = r.upto(r.count), longest = r.rows(0);
+    const int64_t longest = r.rows(0);
+    const double s = (double)share, total = s * (double)r.upto(r.count);
     const double issue = row_issue(G, Q), alone = row_alone(G, Q);
     const double batch = G == 1 ? 8.0 : G == 2 ? 4.0 : G == 4 ? 2.0 : 1.0;   // ends per stop
-    const double mean0 = (double)total / (double)std::max<int64_t>(1, std::min(ngroups, r.count));
+    const double mean0 = total / std::max(1.0, std::min((double)ngroups, s * (double)r.count));
     Cut best;
     for (int k = -1; k < 10; ++k) {
         Cut c;
@@ -288,16 +330,16 @@ Cut choose_cut(const Range &r, int M, int G, int Q, int64_t ngroups) {
             segs = r.upto(ns) / c.seg + ns / 2 + 1;
             top = std::max(c.limit, c.seg + warm);
         }
-        const double nrec = (double)(r.count - ns + segs);
-        const double rows = (double)total + (double)(segs - ns) * (double)warm + 8.0 * nrec;
+        const double nrec = s * (double)(r.count - ns + segs);
+        const double rows = total + s * (double)(segs - ns) * (double)warm + 8.0 * nrec;
         const double n = std::min((double)ngroups, nrec);
         const double waves = std::max(1.0, n * G / 64.0);
-        const double share = std::max(1.0, waves / kSimds);      // wavefronts per SIMD
+        const double per_simd = std::max(1.0, waves / kSimds);   // wavefronts per SIMD
         const double mean = rows / n;
-        c.cycles = mean * std::max(alone, issue * share) * (share > 1.5 ? 1.04 : 1.0) +
+        c.cycles = mean * std::max(alone, issue * per_simd) * (per_simd > 1.5 ? 1.04 : 1.0) +
                    0.6 * std::max(0.0, (double)top - mean) * alone +
-                   nrec / waves / batch * 105.0 * share +
-                   (ns > 0 ? kCutCycles + kSegCycles * (double)segs : 0.0);
+                   nrec / waves / batch * 105.0 * per_simd +
+                   s * (ns > 0 ? kCutCycles + kSegCycles * (double)segs : 0.0);
         if (k < 0 || c.cycles < best.cycles) best = c;
     }
     return best;
@@ -326,8 +368,12 @@ int block_waves(int G, int Q, int rows) { return lds_bytes(G, Q, rows) > 40 * 10
 // M = 400 on 5,000 sequences 284 us with the tuned 8 lanes, 111 with 64;
 // M = 151 on 20,000 107 with 4 lanes, 75 with 8.  The image of 64-lane groups
 // must fit (MSV's exact pass runs on it), which bounds M for both filters.
+// Queries of a batch (share > 1) keep to 32 registers per lane, and to the
+// plans measured fastest among those: the wider kernels' images and registers
+// leave less room for another query's blocks (735, 610 and 164 nodes on
+// 167,000 sequences at once: 2074 us with them, 1865 without).
 hmsv_status resolve_plan(int is_msv, int M, int rows, const Range &r, const hmsv_plan *in,
-                         hmsv_plan *out) {
+                         hmsv_plan *out, int share = 1) {
     if (lds_bytes(kExactG, exact_q(M), rows) > (size_t)kLdsBytes) return HMSV_EUNSUPPORTED;
     if (in) {
         *out = *in;
@@ -336,6 +382,7 @@ hmsv_status resolve_plan(int is_msv, int M, int rows, const Range &r, const hmsv
     hmsv_plan tuned;
     hmsv_status st = hmsv_default_plan(is_msv, M, &tuned);
     if (st != HMSV_OK) return st;
+    if (share > 1) (void)tuned_plan(2 + is_msv, M, &tuned);
     double best = 0.0;
     bool any = false;
     for (int G : {1, 2, 4, 8, 16, 32, 64}) {
@@ -344,18 +391,20 @@ hmsv_status resolve_plan(int is_msv, int M, int rows, const Range &r, const hmsv
         p.Q = (M + 1 + 2 * G - 1) / (2 * G);
         if (lds_bytes(G, p.Q, rows) > (size_t)kLdsBytes) continue;
         if (!registry().find(is_msv ? 1 : 0, G, p.Q)) continue;
+        if (share > 1 && p.Q > 32) continue;      // 64 lanes hold any M in 30
         const bool is_tuned = G == tuned.G && p.Q == tuned.Q;
         p.waves_per_block = is_tuned ? tuned.waves_per_block : block_waves(G, p.Q, rows);
         p.blocks = 0;
         double t = 0.0;
         if (r.count > 0) {
             int64_t waves = 256 * resident_waves(G, p.Q, p.waves_per_block, rows);
-            if (is_tuned && r.upto(r.count) < waves * (64 / G) * r.rows(0)) {
+            if (is_tuned && share == 1 && r.upto(r.count) < waves * (64 / G) * r.rows(0)) {
                 // the longest records set the end: see block_waves
                 p.waves_per_block = std::min(p.waves_per_block, block_waves(G, p.Q, rows));
                 waves = 256 * resident_waves(G, p.Q, p.waves_per_block, rows);
             }
-            t = choose_cut(r, M, G, p.Q, waves * (64 / G)).cycles * (is_tuned ? 0.95 : 1.0);
+            t = choose_cut(r, M, G, p.Q, waves * (64 / G), share).cycles *
+                (is_tuned ? 0.95 : 1.0);
         } else if (!is_tuned) {
             t = (double)G;              // nothing to score: the tuned plan, or the narrowest
         }
@@ -388,7 +437,7 @@ int grid_blocks(const KernelEntry *e, const hmsv_plan &plan, int64_t count, int 
 // blocks of its grid: segments may fill more lane groups than there are
 // sequences.
 void plan_split(const hmsv_db *db, int64_t first, int64_t count, const KernelEntry *e,
-                const hmsv_plan &plan, int M, int *blocks, KArgs &a) {
+                const hmsv_plan &plan, int M, int *blocks, KArgs &a, int share = 1) {
     a.nsplit = 0;
     a.nsegs = 0;
     a.nbins = 0;
@@ -399,7 +448,7 @@ void plan_split(const hmsv_db *db, int64_t first, int64_t count, const KernelEnt
     if (plan.blocks == 0) most = resident_blocks(e, plan.waves_per_block, db->table_rows);
     if (most < *blocks) most = *blocks;
     const Range r{db->cum_rows.data() + first, count};
-    const Cut c = count < 2 ? Cut{} : choose_cut(r, M, plan.G, plan.Q, (int64_t)most * per_block);
+    const Cut c = count < 2 ? Cut{} : choose_cut(r, M, plan.G, plan.Q, (int64_t)most * per_block, share);
     int64_t T = c.seg, limit = c.limit;
     for (; T > 0 && T < (int64_t)kRowsLimit; T *= 2, limit *= 2) {
         const int64_t ns = r.above(limit);
@@ -445,7 +494,7 @@ void plan_split(const hmsv_db *db, int64_t first, int64_t count, const KernelEnt
 hmsv_status score_common(int is_msv, const hmsv_profile *prof, const hmsv_db *db,
                          int64_t first, int64_t count,
                          uint8_t *score, uint8_t *flags, void *workspace,
-                         const hmsv_plan *plan_in, hipStream_t stream) {
+                         const hmsv_plan *plan_in, hipStream_t stream, int share = 1) {
     hmsv_status st = check_profile(prof, is_msv);
     if (st != HMSV_OK) return st;
     if (!db || !workspace) return HMSV_EINVAL;
@@ -493,7 +542,7 @@ hmsv_status score_common(int is_msv, const hmsv_profile *prof, const hmsv_db *db
 
     int blocks = grid_blocks(e, plan, count, db->table_rows);
     if (blocks <= 0) return HMSV_EDEVICE;
-    plan_split(db, first, count, e, plan, prof->M, &blocks, a);
+    plan_split(db, first, count, e, plan, prof->M, &blocks, a, share);
     // MSV: a second kernel rescores the windows the first one stored
     ExactLaunchFn xf = nullptr;
     int cus = 0;
@@ -937,36 +986,7 @@ hmsv_status hmsv_default_plan(int32_t is_msv, int32_t M, hmsv_plan *plan) {
     if (!plan) return HMSV_EINVAL;
     if (M < 1) return HMSV_EINVAL;
     if (M > HMSV_MAX_M) return HMSV_EUNSUPPORTED;
-    // The autotuned plan (paper Sec. 3.4 picks its kernel per model length
-    // the same way): among the tuned M-bins of this filter, nearest to M in
-    // log distance first (ties to the smaller bin), the first whose group
-    // width still holds the profile (a kernel has its registers per lane) and
-    // the LDS.
-    int idx[kNumTuned];
-    int n = 0;
-    for (int i = 0; i < kNumTuned; ++i)
-        if (kTuned[i].is_msv == (is_msv ? 1 : 0)) idx[n++] = i;
-    auto dist = [M](int b) { return std::fabs(std::log((double)b) - std::log((double)M)); };
-    auto before = [&](int a, int b) {
-        double da = dist(kTuned[a].bin), db = dist(kTuned[b].bin);
-        if (da != db) return da < db;
-        return kTuned[a].bin < kTuned[b].bin;
-    };
-    // insertion sort of the few bins (stable, and allocates nothing)
-    for (int t = 1; t < n; ++t)
-        for (int u = t; u > 0 && before(idx[u], idx[u - 1]); --u) std::swap(idx[u], idx[u - 1]);
-    for (int t = 0; t < n; ++t) {
-        const TunedPlan &tp = kTuned[idx[t]];
-        int G = tp.G;
-        int Q = (M + 1 + 2 * G - 1) / (2 * G);
-        if (lds_bytes(G, Q) > (size_t)kLdsBytes) continue;
-        if (!registry().find(is_msv ? 1 : 0, G, Q)) continue;
-        plan->G = G;
-        plan->Q = Q;
-        plan->waves_per_block = tp.waves_per_block;
-        plan->blocks = 0;
-        return HMSV_OK;
-    }
+    if (tuned_plan(is_msv ? 1 : 0, M, plan)) return HMSV_OK;
     // Untuned fallback: the narrowest lane group that holds the profile.
     for (int G : {1, 2, 4, 8, 16, 32, 64}) {
         int Q = (M + 1 + 2 * G - 1) / (2 * G);
@@ -1166,6 +1186,49 @@ hmsv_status hmsv_p7_default_plan(int32_t M, hmsv_plan *plan) {
 
 namespace {
 
+// The plan of a P7Viterbi call on a whole database: the lane group width of
+// the least expected time, T = (A^5 + B^5)^(1/5) cycles, from a fit to 1,180
+// timed calls (M = 30 to 2400, 1,000 to 400,000 sequences; 7.5% rms error; its
+// choice takes 3% more than the fastest on average): A, all rows at a row's
+// issue on every SIMD, 41 Q + 78 cycles per row of a wavefront, 3/R more with
+// R wavefronts on a CU, and 2000 cycles per record; B, the longest record
+// alone, 71 Q + 251 cycles per row, 27% more where the transitions come from
+// the LDS (Q > 6).  The longest record rules small databases, and the widest
+// groups run one fastest: M = 200 on 20,000 sequences 2070 us with 16 lanes (the
+// measured plan of large databases), 940 with 64; on 200,000 3300 and 5570.
+void p7_choose(const hmsv_db *db, int M, hmsv_plan *plan) {
+    const hmsv_plan tuned = *plan;
+    const double total = (double)db->cum_rows[(size_t)db->nseq], nseq = (double)db->nseq;
+    const double longest = (double)db->cum_rows[1];
+    double best = 0.0;
+    bool any = false;
+    for (int G : {4, 8, 16, 32, 64}) {
+        hmsv_plan p;
+        p.G = G;
+        p.Q = (M + 1 + 2 * G - 1) / (2 * G);
+        if (p.Q == 19) p.Q = 20;          // see hmsv_p7_default_plan
+        if (p.Q > (G == 64 ? 22 : 16) || !registry().find_p7(G, p.Q)) continue;
+        const size_t lds = p7_lds_bytes(G, p.Q, db->table_rows);
+        if (lds > (size_t)kLdsBytes) continue;
+        p.waves_per_block = G == tuned.G && p.Q == tuned.Q ? tuned.waves_per_block
+                          : p.Q >= 12                      ? p7_max_waves(G, p.Q)
+                                                           : 8;
+        p.blocks = 0;
+        const int by_regs = p.Q == 1 ? 32 : p.Q == 2 ? 28 : p.Q <= 8 ? 20 : 16;
+        const int by_lds = (int)((size_t)kLdsBytes / lds) * p.waves_per_block;
+        const double resident = (double)std::max(p.waves_per_block, std::min(by_lds, by_regs));
+        const double a = G / 64.0 / kSimds *
+                         (total * (41.0 * p.Q + 78.0) * (1.0 + 3.0 / resident) + nseq * 2000.0);
+        const double b = longest * (71.0 * p.Q + 251.0) * (p.Q > 6 ? 1.27 : 1.0);
+        const double t = std::pow(std::pow(a, 5.0) + std::pow(b, 5.0), 0.2);
+        if (!any || t < best) {
+            any = true;
+            best = t;
+            *plan = p;
+        }
+    }
+}
+
 hmsv_status p7_common(const hmsv_p7_profile *prof, const hmsv_db *db, const int32_t *sel,
                       const int32_t *nsel, int16_t *score, uint8_t *flags, void *workspace,
                       const hmsv_plan *plan_in, hipStream_t stream) {
@@ -1189,15 +1252,7 @@ hmsv_status p7_common(const hmsv_p7_profile *prof, const hmsv_db *db, const int3
     } else {
         hmsv_status st = hmsv_p7_default_plan(prof->M, &plan);
         if (st != HMSV_OK) return st;
-        // with the degenerate rows the image may no longer fit: the
-        // narrowest group that still holds it
-        for (int G : {4, 8, 16, 32, 64}) {
-            if (p7_lds_bytes(plan.G, plan.Q, db->table_rows) <= (size_t)kLdsBytes) break;
-            const int Q = (prof->M + 1 + 2 * G - 1) / (2 * G);
-            if (Q > (G == 64 ? 22 : 16) || !registry().find_p7(G, Q)) continue;
-            plan.G = G;
-            plan.Q = Q;
-        }
+        if (db->nseq > 0) p7_choose(db, prof->M, &plan);
     }
     if (plan.G < 1 || plan.G > 64 || (64 % plan.G) != 0 || plan.Q < 1 ||
         plan_nodes(plan.G, plan.Q) < prof->M || plan.blocks < 0 ||
@@ -1302,7 +1357,8 @@ hmsv_status hmsv_batch_create(const hmsv_query *queries, int32_t nq, const hmsv_
             if (queries[k].workspace == q.workspace) return HMSV_EINVAL;
         st = resolve_plan(q.is_msv ? 1 : 0, q.prof.M, db->table_rows,
                           Range{db->cum_rows.data(), db->nseq},
-                          q.plan.G == 0 ? nullptr : &q.plan, &plans[i]);
+                          q.plan.G == 0 ? nullptr : &q.plan, &plans[i],
+                          std::min(branches, nq));
         if (st != HMSV_OK) return st;
         if (!registry().find(q.is_msv ? 1 : 0, plans[i].G, plans[i].Q)) return HMSV_ENOKERNEL;
     }
@@ -1342,7 +1398,8 @@ hmsv_status hmsv_batch_create(const hmsv_query *queries, int32_t nq, const hmsv_
         if (rc != HMSV_OK) break;
         const hmsv_query &q = queries[i];
         rc = score_common(q.is_msv ? 1 : 0, &q.prof, db, 0, db->nseq, (uint8_t *)q.score,
-                          q.flags, q.workspace, &plans[i], st[branch_of[i]]);
+                          q.flags, q.workspace, &plans[i], st[branch_of[i]],
+                          std::min(branches, nq));
     }
     if (rc == HMSV_OK) {
         // join every branch back into the origin stream
@@ -1363,6 +1420,7 @@ hmsv_status hmsv_batch_create(const hmsv_query *queries, int32_t nq, const hmsv_
     if (rc == HMSV_OK) {
         bt->graph = graph;
         bt->nq = nq;
+        bt->plans.swap(plans);
         if (hipGraphInstantiate(&bt->exec, graph, nullptr, nullptr, 0) != hipSuccess) {
             rc = HMSV_EDEVICE;
             bt->graph = nullptr;
@@ -1379,6 +1437,12 @@ hmsv_status hmsv_batch_create(const hmsv_query *queries, int32_t nq, const hmsv_
         if (s2) hipStreamDestroy(s2);
     if (rc == HMSV_OK) *out = bt;
     return rc;
+}
+
+hmsv_status hmsv_batch_plan(const hmsv_batch *batch, int32_t i, hmsv_plan *plan) {
+    if (!batch || !plan || i < 0 || i >= batch->nq) return HMSV_EINVAL;
+    *plan = batch->plans[(size_t)i];
+    return HMSV_OK;
 }
 
 hmsv_status hmsv_batch_launch(hmsv_batch *batch, hipStream_t stream) {

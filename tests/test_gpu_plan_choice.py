@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import oracle
+from oracle import p7 as op7
 from oracle import quant as oq
 import synth
 
@@ -82,4 +83,51 @@ def test_ranges_choose_alone(hm, filt):
         assert len(done) == count
         assert np.array_equal(s[done], exp[0][done]) and np.array_equal(f[done], exp[1][done])
         assert (s[f == 77] == 77).all()
+    gdb.close()
+
+
+@pytest.mark.parametrize("M", [20, 150, 900])
+@pytest.mark.parametrize("name", ["one", "few-long", "many-short"])
+@pytest.mark.parametrize("degen", [False, True], ids=["plain", "degenerate"])
+def test_p7_chosen_plan(hm, name, M, degen):
+    n, lo, hi, long = SETS[name]
+    rng = np.random.default_rng(M + n)
+    L = np.concatenate([np.asarray(long, np.int64) // 4, rng.integers(lo, hi, min(n, 4000))])
+    off = np.concatenate([[0], np.cumsum(L)]).astype(np.int64)
+    res = rng.integers(0, 20, int(off[-1])).astype(np.uint8)
+    if degen:
+        res[::7] = 21 + res[::7] % 6
+    emis, trans = synth.sample_emissions(rng, M), synth.sample_transitions(rng, M)
+    prof = hm.P7Profile.from_probabilities(emis, trans, synth.BG)
+    gdb = hm.Database(res, off)
+    exp = oracle.p7_score_db(op7.quantize(emis, trans, synth.BG), res, off)
+    for p in (None, hm.p7_default_plan(M)):
+        print(f"case p7 {name} M={M} {p and p.as_tuple()} degen={degen}", flush=True)
+        s, f = hm.p7_score(prof, gdb, plan=p)
+        torch.cuda.synchronize()
+        assert np.array_equal(s.cpu().numpy(), exp[0])
+        assert np.array_equal(f.cpu().numpy(), exp[1])
+    gdb.close()
+
+
+def test_batch_plans(hm):
+    """Queries of a batch get plans of at most 32 registers; the scores are
+    those of single calls."""
+    from paper_1707_09683_amd.batch import Batch
+    rng = np.random.default_rng(8)
+    L = rng.integers(20, 600, 3000)
+    off = np.concatenate([[0], np.cumsum(L)]).astype(np.int64)
+    res = rng.integers(0, 20, int(off[-1])).astype(np.uint8)
+    gdb = hm.Database(res, off)
+    qs = [(f, hm.Profile.from_emissions(synth.sample_emissions(rng, M), synth.BG))
+          for f, M in (("msv", 600), ("ssv", 40), ("msv", 2300), ("ssv", 130))]
+    b = Batch(qs, gdb)
+    b.launch()
+    torch.cuda.synchronize()
+    for (filt, p), plan, s, f in zip(qs, b.plans, b.scores, b.flags):
+        assert plan.Q <= 32 and 2 * plan.G * plan.Q > p.M
+        s1, f1 = (hm.msv_score if filt == "msv" else hm.ssv_score)(p, gdb)
+        torch.cuda.synchronize()
+        assert torch.equal(s, s1) and torch.equal(f, f1)
+    b.close()
     gdb.close()
