@@ -478,13 +478,14 @@ filter_kernel(KArgs a) {
         const int r = g < nlong ? nv - 1 - nlong - g : i2 + ngroups - 1 - g;
         return g < nlong ? (r >= i3 ? r : kNone) : (r < nv - nlong ? r : kNone);
     };
-    // Claims come from up to kQueues counters, each on its own 128-byte line:
+    // Claims come from a.parts counters, one or kQueues, each on its own 128-byte line:
     // counter p hands out records p, p + P, ... of those in between to 1/P of the
     // blocks.  One counter takes an atomic every 2 to 4 ns, which bounded calls
     // with many short rows: SSV at M = 100, 500,000 sequences with 16 counters
     // 1.73x as fast on 64-lane groups, 1.67x on 32, 1.51x on 16, 1.30x on 8.
-    // A call that needs no claims makes none.
-    const int parts = (int)gridDim.x < kQueues ? (int)gridDim.x : kQueues;
+    // (With one, no part of the grid can run out of records before another:
+    // the host picks by the rate.)  A call that needs no claims makes none.
+    const int parts = (int)gridDim.x < a.parts ? (int)gridDim.x : a.parts;
     const int part = (int)blockIdx.x % parts;
     uint32_t *counter = a.counter + part * 32;
     const bool claims = i3 < nv - 2 * nlong;

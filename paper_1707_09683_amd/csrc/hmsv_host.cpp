@@ -476,6 +476,13 @@ void plan_split(const hmsv_db *db, int64_t first, int64_t count, const KernelEnt
     const int64_t nrec = count - a.nsplit + a.nsegs;
     if (plan.blocks == 0)
         *blocks = (int)std::min<int64_t>(most, (nrec + per_block - 1) / per_block);
+    // One counter serves a claim every 2 to 4 ns; with sixteen, one for each
+    // 1/16 of the blocks, some blocks run out before others.  M = 400 on 500,000
+    // sequences (3.4 ns per record) 1705 us with sixteen, 1680 with one;
+    // M = 2400 on 60,000 (24 ns) 1456 and 1432; M = 30 on 500,000 (0.5 ns) 229
+    // and 231, M = 100 on 200,000 (1.2 ns) 238 and 239.
+    constexpr double kCyclesPerNs = 2.35, kClaimNs = 3.0;
+    a.parts = c.cycles >= kClaimNs * kCyclesPerNs * (double)share * (double)nrec ? 1 : kQueues;
     // Groups that start on a record of more than half the mean work go on with
     // the shortest records.  With six or more
     // records per group all do: wavefronts advance unequally (the oldest of a

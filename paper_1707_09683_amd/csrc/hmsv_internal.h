@@ -82,6 +82,7 @@ struct KArgs {
     int32_t nsegs;
     int32_t seg_rows;      // rows per segment (multiple of 16)
     int32_t warm;          // rows before a segment (multiple of 16, >= M - 1)
+    int32_t parts;         // claim counters in use, 1..kQueues
     int32_t nlong;         // groups whose first record is a large part of the mean
                            // work per group (at most the grid's groups)
     // Split sequence t has v = ceil(rows / seg_rows) segments, which take
