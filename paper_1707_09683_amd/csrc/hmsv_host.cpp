@@ -258,6 +258,7 @@ bool tuned_plan(int kind, int M, hmsv_plan *plan) {
 //  * alone on its SIMD, a wavefront takes 31 + 10.5 Q cycles per row (the chain
 //    from one row to the next and the reads of scores); a record longer than
 //    the mean work per group adds 0.6 of that per row beyond it;
+//  * with n wavefronts on a SIMD, 0.65 / n^2 more (what they don't hide);
 //  * a sequence's end stops its wavefront for 105 cycles per wavefront on the
 //    SIMD.
 constexpr double kSimds = 1024.0;            // 256 CUs x 4
@@ -336,7 +337,8 @@ Cut choose_cut(const Range &r, int M, int G, int Q, int64_t ngroups, int share =
         const double waves = std::max(1.0, n * G / 64.0);
         const double per_simd = std::max(1.0, waves / kSimds);   // wavefronts per SIMD
         const double mean = rows / n;
-        c.cycles = mean * std::max(alone, issue * per_simd) * (per_simd > 1.5 ? 1.04 : 1.0) +
+        const double exposed = per_simd > 1.5 ? 1.0 + 0.65 / (per_simd * per_simd) : 1.0;
+        c.cycles = mean * std::max(alone, issue * per_simd) * exposed +
                    0.6 * std::max(0.0, (double)top - mean) * alone +
                    nrec / waves / batch * 105.0 * per_simd +
                    s * (ns > 0 ? kCutCycles + kSegCycles * (double)segs : 0.0);
@@ -353,11 +355,16 @@ int resident_waves(int G, int Q, int wpb, int rows) {
     return std::max(wpb, std::min(by_lds, by_regs / wpb * wpb));
 }
 
-// Wavefronts per block of an untuned plan: four, one per SIMD, where several
-// images fit a CU.  (The wavefronts of a block start on neighbouring records,
-// so large blocks put the longest ones on the same CU: M = 2400 on 60,000
-// sequences 1.45 ms with 8 wavefronts, 1.69 with 12, 2.03 with 16.)
-int block_waves(int G, int Q, int rows) { return lds_bytes(G, Q, rows) > 40 * 1024 ? 8 : 4; }
+// Wavefronts per block of an untuned plan: four, one per SIMD, unless blocks of
+// eight put more on a CU: the image decides how many blocks fit (M = 265,
+// 201,525 sequences with degenerate codes, 4 lanes of 34 registers: 713 us with
+// four, 588 with eight; M = 500, 8 lanes of 32: 950 and 895, without
+// degenerate codes 886 and 901).  More than eight lose: M = 2400 on 60,000 1.45
+// ms with 8, 1.69 with 12, 2.03 with 16 (on neighbouring records).
+int block_waves(int G, int Q, int rows) {
+    if (lds_bytes(G, Q, rows) > 40 * 1024) return 8;
+    return resident_waves(G, Q, 8, rows) > resident_waves(G, Q, 4, rows) ? 8 : 4;
+}
 
 // The plan of a call on a range of a database whose images need `rows` table
 // rows: the caller's, or else the lane group width of the least expected time.
@@ -393,7 +400,9 @@ hmsv_status resolve_plan(int is_msv, int M, int rows, const Range &r, const hmsv
         if (!registry().find(is_msv ? 1 : 0, G, p.Q)) continue;
         if (share > 1 && p.Q > 32) continue;      // 64 lanes hold any M in 30
         const bool is_tuned = G == tuned.G && p.Q == tuned.Q;
-        p.waves_per_block = is_tuned ? tuned.waves_per_block : block_waves(G, p.Q, rows);
+        // (the tuned block size was measured with 21 table rows)
+        p.waves_per_block = is_tuned && rows == kRows ? tuned.waves_per_block
+                                                      : block_waves(G, p.Q, rows);
         p.blocks = 0;
         double t = 0.0;
         if (r.count > 0) {
