@@ -49,10 +49,12 @@ sys.path.insert(0, ROOT)
 # cells per instruction): one saturating (clamped) add of the per-node score
 # per cell pair, plus half of a three-way max into scE -> 1.5 per pair for
 # both filters.  (MSV's max with scB folds into the cell representation
-# while scB is fixed: cells are kept relative to scB.)
+# while scB is fixed: cells are kept relative to scB.)  P7Viterbi's cost form:
+# six saturating subtracts or adds and three and a half three- or two-way
+# maxima per cell pair, 9.5.
 CUS, LANES, CLOCK_HZ = 256, 64, 2.4e9
 PEAK_INSTR = CUS * LANES * CLOCK_HZ              # 39.3e12 lane-instructions/s
-INSTR_PER_CELL = {"msv": 0.75, "ssv": 0.75, "p7": 7.0}
+INSTR_PER_CELL = {"msv": 0.75, "ssv": 0.75, "p7": 4.75}
 # The same peak counted in the paper's per-cell operations (Alg. 2: four
 # 8-bit operations per MSV cell; Alg. 7: two per SSV cell) at two 16-bit
 # lanes per packed instruction: 19.7e12 MSV and 39.3e12 SSV cells/s.  The
@@ -205,13 +207,13 @@ def time_plain(hm, torch, filt, prof, gdb, plan, steps, warmup):
 def layout_leg(hm, h):
     """Padding of the database layouts on the headline database: this
     library's records (each sequence's rows rounded up to the kernel's
-    16-row step, or 8 for groups of 16+ lanes) against the paper's
+    16-row step) against the paper's
     warp-based blocks (Alg. 1) at the paper's K40 shape (15 SMX x 32 warps,
     128 columns) and at this GPU's (the headline plan's resident wavefronts,
     64/G sequences each).  Host arithmetic only."""
     L = np.asarray(h["db"].lengths, dtype=np.int64)
     G, Q, wpb = h["plan"].G, h["plan"].Q, h["plan"].waves_per_block
-    step = 16 if G < 16 else 8
+    step = 16
     rows = np.maximum(4, (L + 3) // 4 * 4)
     run = int(((rows + step - 1) // step * step).sum())
     real = int(L.sum())
@@ -319,7 +321,7 @@ def ssv_leg(a, hm, torch, synth, h):
 
 def p7_leg(a, hm, torch, synth, h):
     """P7Viterbi on the same 500k database for four profile lengths:
-    throughput, roofline fraction (7 packed instructions per cell) and oracle
+    throughput, roofline fraction (4.75 packed instructions per cell) and oracle
     parity: every sequence at M = 400, a seeded sample of 5,000 sequences at
     the other lengths."""
     out = []

@@ -30,8 +30,8 @@
 //    out [row][chunk][copy][lane][W] so each lane reads W consecutive dwords
 //    and the groups served by one LDS read pass (256 bytes) use disjoint
 //    banks: no bank conflicts between groups reading different rows.
-//  * Sequences are handed out longest first from a global counter as groups
-//    finish (replaces the pre-packed warp blocks of Alg. 1).
+//  * Sequences are handed out longest first from one or sixteen counters as
+//    groups finish (replaces the pre-packed warp blocks of Alg. 1).
 //  * MSV special states: scB fixed for every sequence first, then an exact
 //    rescoring of short windows of the few sequences where the J state may
 //    open, in a second launch (see filter_kernel).  When scB rises by
@@ -176,7 +176,12 @@ __device__ __forceinline__ uint32_t slot_bits(const KArgs &a, int x, int s) {
 }
 
 // Ring of score chunks of the lanes with more than kRingQ registers, which
-// read scores kRing - 1 chunks of four ahead instead of whole rows.
+// read scores kRing - 1 chunks of four ahead instead of whole rows: those would
+// not fit beside the cells, and VALU issue is the bound, so three chunks in
+// flight (24 instructions) cover an LDS read where other wavefronts don't.
+// Fewer lanes per sequence leave less of a row's fixed work: MSV on 500,000
+// sequences at M = 1536 / 2400 / 3839 on 32 or 64 lanes of up to 32 registers
+// 40.9 / 40.8 / 41.9 TCUPS, on 16 or 32 lanes of up to 60 43.1 / 43.0 / 45.7.
 constexpr int kRing = 4;
 constexpr int kRingQ = 32;
 
@@ -261,9 +266,9 @@ struct Lane {
     }
 
     // One row, in place, registers in descending order (register q takes the
-    // old q - 1), its scores read kRing - 1 chunks ahead: buf holds the row's first kRing - 1 (its last chunks),
-    // in ring slots SLOT0, SLOT0 + 1, ...; the turns of the rest read the first
-    // ones of the next row (residue xn).
+    // old q - 1), its scores read kRing - 1 chunks ahead: buf holds the row's
+    // first kRing - 1 (its last chunks), in ring slots SLOT0, SLOT0 + 1, ...;
+    // the turns of the rest read the first ones of the next row (residue xn).
     template <int SLOT0>
     __device__ __forceinline__ void row_ahead(const uint32_t *TW, uint32_t x, uint32_t xn,
                                               uint32_t (&buf)[kRing][4]) {
@@ -295,7 +300,10 @@ struct Lane {
 
 // A wavefront's number in its grid: four of each block (one per SIMD of its
 // CU), then the next four of each, and so on.  Lane groups of lower numbers
-// take longer records, so each SIMD of a CU gets some of each length.
+// take longer records, so each SIMD of a CU gets some of each length.  (SSV at
+// M = 2400 on 3,000 sequences, blocks of 8: 387 us with a block's wavefronts on
+// neighbouring records, 310 so; M = 151 on 20,000: 66 and 66, and 81 with all
+// blocks' first wavefronts before any second one, on one SIMD of each CU.)
 __device__ __forceinline__ int wave_rank() {
     const int w = (int)(threadIdx.x >> 6), per_block = (int)(blockDim.x >> 6);
     const int four = w & ~3;
@@ -361,7 +369,7 @@ constexpr int kExitGroups = G == 1 ? 8 : G == 2 ? 4 : G == 4 ? 2 : 1;
 constexpr int kPipeQ = 17;
 
 // One filter launch.  Every lane group pulls sequences (longest first)
-// from the call's range and runs their rows in steps of 4K residues.
+// from the call's range and runs their rows in steps of 16 residues.
 //
 // kMSV runs a sequence with scB fixed at sat0(base - tjb - tbm).  Cells
 // relative to scB then follow the SSV-like recurrence u = max(0, u + dbias
@@ -478,8 +486,8 @@ filter_kernel(KArgs a) {
         const int r = g < nlong ? nv - 1 - nlong - g : i2 + ngroups - 1 - g;
         return g < nlong ? (r >= i3 ? r : kNone) : (r < nv - nlong ? r : kNone);
     };
-    // Claims come from a.parts counters, one or kQueues, each on its own 128-byte line:
-    // counter p hands out records p, p + P, ... of those in between to 1/P of the
+    // Claims come from a.parts counters, one or kQueues, each on its own
+    // 128-byte line: counter p hands out records p, p + P, ... of those in between to 1/P of the
     // blocks.  One counter takes an atomic every 2 to 4 ns, which bounded calls
     // with many short rows: SSV at M = 100, 500,000 sequences with 16 counters
     // 1.73x as fast on 64-lane groups, 1.67x on 32, 1.51x on 16, 1.30x on 8.
