@@ -316,12 +316,12 @@ Cut choose_cut(const Range &r, int M, int G, int Q, int64_t ngroups, int share =
     const double batch = G == 1 ? 8.0 : G == 2 ? 4.0 : G == 4 ? 2.0 : 1.0;   // ends per stop
     const double mean0 = total / std::max(1.0, std::min((double)ngroups, s * (double)r.count));
     Cut best;
-    for (int k = -1; k < 10; ++k) {
+    for (int k = -1; k < 12; ++k) {
         Cut c;
         int64_t ns = 0, segs = 0, top = longest;
         if (k >= 0) {
-            // limits 2, 1.41, 1, 0.71, ... times the mean work per group
-            c.limit = (int64_t)(mean0 * std::pow(2.0, 1.0 - 0.5 * k)) & ~(int64_t)15;
+            // limits 4, 2.83, 2, 1.41, 1, ... times the mean work per group
+            c.limit = (int64_t)(mean0 * std::pow(2.0, 2.0 - 0.5 * k)) & ~(int64_t)15;
             c.seg = std::max(c.limit - warm, std::max(kMinSeg, warm / 4)) & ~(int64_t)15;
             c.limit = std::max(c.limit, c.seg);
             if (c.limit >= longest) continue;
