@@ -10,6 +10,7 @@ ImportError: there is no fallback implementation.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 from typing import NamedTuple
 import os
@@ -339,17 +340,25 @@ def _scratch(device, nseq: int) -> torch.Tensor:
     return torch.empty(workspace_bytes(nseq), dtype=torch.uint8, device=device)
 
 
+def _owner(stream):
+    """A call allocates tensors of its own on the stream that it runs on: the
+    caching allocator hands a freed block out again as soon as the work of the
+    stream it was allocated on allows, whatever other streams still do with it."""
+    return torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext()
+
+
 def _score(filt, profile: Profile, db: Database, score, flags, workspace, plan, stream,
            rng=None):
     dev = profile.device
     n = db.nseq
     sdt = torch.uint8 if filt == "msv" else torch.int8
-    if score is None:
-        score = torch.empty(n, dtype=sdt, device=dev)
-    if flags is None:
-        flags = torch.empty(n, dtype=torch.uint8, device=dev)
-    if workspace is None:
-        workspace = _scratch(dev, n)
+    with _owner(stream):
+        if score is None:
+            score = torch.empty(n, dtype=sdt, device=dev)
+        if flags is None:
+            flags = torch.empty(n, dtype=torch.uint8, device=dev)
+        if workspace is None:
+            workspace = _scratch(dev, n)
     if score.dtype != sdt or flags.dtype != torch.uint8:
         raise TypeError("score/flags dtype")
     if score.numel() < n or flags.numel() < n or not score.is_contiguous() \
@@ -487,12 +496,13 @@ def p7_score(profile: P7Profile, db: Database, score=None, flags=None, workspace
     sequence, in the database's original order."""
     dev = profile.device
     n = db.nseq
-    if score is None:
-        score = torch.empty(n, dtype=torch.int16, device=dev)
-    if flags is None:
-        flags = torch.empty(n, dtype=torch.uint8, device=dev)
-    if workspace is None:
-        workspace = _scratch(dev, n)
+    with _owner(stream):
+        if score is None:
+            score = torch.empty(n, dtype=torch.int16, device=dev)
+        if flags is None:
+            flags = torch.empty(n, dtype=torch.uint8, device=dev)
+        if workspace is None:
+            workspace = _scratch(dev, n)
     if score.dtype != torch.int16 or flags.dtype != torch.uint8:
         raise TypeError("score must be int16 and flags uint8")
     if score.numel() < n or flags.numel() < n or not score.is_contiguous() \
@@ -530,12 +540,13 @@ def select(db: Database, score, flags, filt, threshold, positions=None, count=No
     n = db.nseq
     _device_tensor(score, torch.uint8 if filt == "msv" else torch.int8, n, dev, "score")
     _device_tensor(flags, torch.uint8, n, dev, "flags")
-    if positions is None:
-        positions = torch.empty(max(n, 1), dtype=torch.int32, device=dev)
-    if count is None:
-        count = torch.empty(1, dtype=torch.int32, device=dev)
-    if workspace is None:
-        workspace = _scratch(dev, n)
+    with _owner(stream):
+        if positions is None:
+            positions = torch.empty(max(n, 1), dtype=torch.int32, device=dev)
+        if count is None:
+            count = torch.empty(1, dtype=torch.int32, device=dev)
+        if workspace is None:
+            workspace = _scratch(dev, n)
     _device_tensor(positions, torch.int32, n, dev, "positions")
     _device_tensor(count, torch.int32, 1, dev, "count")
     if workspace.device != dev or workspace.numel() * workspace.element_size() \
@@ -563,7 +574,8 @@ def p7_score_selected(profile: P7Profile, db: Database, positions, count, score,
     _device_tensor(score, torch.int16, n, dev, "score")
     _device_tensor(flags, torch.uint8, n, dev, "flags")
     if workspace is None:
-        workspace = _scratch(dev, n)
+        with _owner(stream):
+            workspace = _scratch(dev, n)
     if workspace.device != dev or workspace.numel() * workspace.element_size() \
             < workspace_bytes(n):
         raise ValueError("workspace too small or on another device")
@@ -602,9 +614,7 @@ def pipeline(filt, profile: Profile, p7_profile: P7Profile, db: Database, thresh
     n = db.nseq
     if stream is None:
         stream = torch.cuda.current_stream(dev)
-    # outputs allocated on the stream that writes them (the caching
-    # allocator reuses a block only after that stream's work on it)
-    with torch.cuda.stream(stream):
+    with _owner(stream):
         if workspace is None:
             workspace = _scratch(dev, n)
         fs = torch.empty(n, dtype=torch.uint8 if filt == "msv" else torch.int8, device=dev)
