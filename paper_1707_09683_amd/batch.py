@@ -11,7 +11,7 @@ import ctypes
 
 import torch
 
-from . import (_CProfile, Plan, Profile, Database, _lib, _check, workspace_bytes)
+from . import (_CProfile, Plan, Profile, Database, _lib, _check, _scratch)
 
 
 class _CQuery(ctypes.Structure):
@@ -55,7 +55,7 @@ class Batch:
             sdt = torch.uint8 if filt == "msv" else torch.int8
             s = torch.empty(n, dtype=sdt, device=dev)
             f = torch.empty(n, dtype=torch.uint8, device=dev)
-            ws = torch.zeros(workspace_bytes(n), dtype=torch.uint8, device=dev)
+            ws = _scratch(dev, n)
             p = plans[i] if plans is not None and plans[i] is not None else Plan()
             self.scores.append(s)
             self.flags.append(f)
@@ -77,9 +77,22 @@ class Batch:
             _check(_lib.hmsv_batch_plan(h, i, ctypes.byref(p)), "hmsv_batch_plan")
             self.plans.append(p)
         self.device = dev
+        # streams that may use the buffers: the one they were allocated on, and
+        # those that launch() has ordered after it
+        own = torch.cuda.current_stream(dev)
+        self._ready = own.record_event()
+        self._streams = {own.cuda_stream}
 
     def launch(self, stream=None):
         stream = stream or torch.cuda.current_stream(self.device)
+        if stream.cuda_stream not in self._streams:
+            # what the buffers' memory held before may still be in use on the
+            # stream that allocated them, and must not be handed out again while
+            # this one runs
+            stream.wait_event(self._ready)
+            for t in (*self.scores, *self.flags, *self.workspaces):
+                t.record_stream(stream)
+            self._streams.add(stream.cuda_stream)
         with torch.cuda.device(self.device):
             _check(_lib.hmsv_batch_launch(self._h, ctypes.c_void_p(stream.cuda_stream)),
                    "hmsv_batch_launch")

@@ -104,6 +104,8 @@ class _Slot:
         self.h_score = torch.empty(n, dtype=torch.uint8, pin_memory=True)
         self.h_flags = torch.empty(n, dtype=torch.uint8, pin_memory=True)
         self.stream = torch.cuda.Stream(device)
+        # (the buffers' memory may still be in use, or being cleared, there)
+        self.stream.wait_stream(torch.cuda.current_stream(device))
         self.busy = False
 
     @staticmethod

@@ -1,4 +1,5 @@
-"""A call given a stream allocates the tensors it makes itself on that stream:
+"""A call given a stream allocates the tensors it makes itself on that stream,
+and a batch orders and keeps its buffers for every stream that launches it:
 the caching allocator hands out a freed block as soon as the stream it was
 allocated on allows.  On the CPU, with the stream and library calls replaced
 by records of them."""
@@ -90,3 +91,20 @@ def test_own_tensors_come_from_the_calls_stream(cpu, side):
         made.clear()
         call()
         assert made and set(made) == {2 if side else 1}, made
+
+
+def test_batch_orders_other_streams(cpu, monkeypatch):
+    hm, batch, _ = cpu
+    db, prof, _ = inputs(hm)
+    kept = []
+    monkeypatch.setattr(torch.Tensor, "record_stream", lambda t, s: kept.append((t.data_ptr(), s)))
+    b = batch.Batch([("msv", prof), ("ssv", prof)], db)
+    b.launch()
+    assert not kept
+    other = Stream(3)
+    for _ in range(2):
+        b.launch(other)
+    assert other.waited == [("event of", 1)]
+    assert {p for p, s in kept if s is other} == {t.data_ptr() for t in
+                                                  (*b.scores, *b.flags, *b.workspaces)}
+    assert len(kept) == 6
