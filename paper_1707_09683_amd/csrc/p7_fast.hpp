@@ -252,10 +252,12 @@ __global__ void __launch_bounds__(THREADS) p7_fast_kernel(P7Args a) {
             // residues of the next step (the database stores every sequence
             // in whole 16-residue steps plus 16 more bytes)
             const uint4 wn = *(const uint4 *)(a.res + off + 16u);
-            // the frame back to F at kP7Base
+            // the frame back to F at kP7Base (never down: a new M is at most a
+            // cell or F of the row before, all at most lvl, so neither lvl nor
+            // F rises within a step)
             {
                 const int up = kP7Base - (int)(F & 0xffffu);
-                const uint32_t add = splat_u(up > 0 ? up : 0);
+                const uint32_t add = splat_u(up);
                 fbase -= up;
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
@@ -267,19 +269,6 @@ __global__ void __launch_bounds__(THREADS) p7_fast_kernel(P7Args a) {
                 sD = uadd(sD, add);
                 c = uadd(c, add);
                 lvl = uadd(lvl, add);
-                if (__any(up < 0)) {         // J rose in the step before
-                    const uint32_t sub = splat_u(up < 0 ? -up : 0);
-#pragma unroll
-                    for (int q = 0; q < Q; ++q) {
-                        M[q] = usub(M[q], sub);
-                        I[q] = usub(I[q], sub);
-                        D[q] = usub(D[q], sub);
-                    }
-                    sM = usub(sM, sub);
-                    sD = usub(sD, sub);
-                    c = usub(c, sub);
-                    lvl = usub(lvl, sub);
-                }
             }
             const int last = len - done - 1;         // the sequence's last row, if in this step
             const bool ends = __any(active && last < 16);
