@@ -911,7 +911,9 @@ hmsv_status hmsv_db_create(const uint8_t *res, const int64_t *offsets, int64_t n
     std::stable_sort(order.begin(), order.end(),
                      [&](int64_t a, int64_t b) { return len[a] > len[b]; });
     std::vector<SeqRec> recs((size_t)nseq);
-    std::vector<uint32_t> p7len((size_t)std::max<int64_t>(1, nseq), 0u);
+    // the length models, then P7Args::gentle
+    const size_t np7 = (size_t)std::max<int64_t>(1, nseq);
+    std::vector<uint32_t> p7len(np7 + kP7Loops, 0u);
     uint64_t total = 0, rows = 0;
     std::vector<int64_t> cum_rows((size_t)nseq + 1, 0);
     for (int64_t t = 0; t < nseq; ++t) {
@@ -922,7 +924,8 @@ hmsv_status hmsv_db_create(const uint8_t *res, const int64_t *offsets, int64_t n
         recs[t].rt = (uint32_t)r | ((uint32_t)hmsv_tjb(len[i]) << 24);
         recs[t].id = (uint32_t)i;
         p7len[t] = p7_lenmodel(len[i]);
-
+        const int cost = -(int)(int16_t)(p7len[t] & 0xffffu);
+        if (cost < kP7Loops) p7len[np7 + (size_t)cost] = (uint32_t)(t + 1);
         // 16-byte aligned; the rows rounded up to 16, then 16 bytes of code 20
         // (narrow lane groups run 16 rows per step and read past the end)
         total += ((r + 15) & ~(uint64_t)15) + 16;
@@ -930,6 +933,8 @@ hmsv_status hmsv_db_create(const uint8_t *res, const int64_t *offsets, int64_t n
         cum_rows[(size_t)t + 1] = (int64_t)rows;
         if (total >= ((uint64_t)1 << 32) - 64) return HMSV_EUNSUPPORTED;
     }
+    for (int v = 1; v < kP7Loops; ++v)
+        p7len[np7 + v] = std::max(p7len[np7 + v], p7len[np7 + v - 1]);
     const uint32_t pad_off = (uint32_t)total;
     const size_t bytes = (size_t)total + 64;
     std::vector<uint8_t> packed(bytes, kInvalidCode);
@@ -1300,6 +1305,7 @@ hmsv_status p7_common(const hmsv_p7_profile *prof, const hmsv_db *db, const int3
     a.res = db->d_res;
     a.seqs = db->d_seqs;
     a.lenmodel = db->d_p7len;
+    a.gentle = db->d_p7len + std::max<int64_t>(1, db->nseq);
     a.nseq = (int32_t)db->nseq;
     a.pad_off = db->pad_off;
     a.score = score;

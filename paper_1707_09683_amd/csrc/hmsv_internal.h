@@ -204,6 +204,8 @@ struct P7Args {
     const uint8_t *res;    // packed residues
     const SeqRec *seqs;    // records in processing order
     const uint32_t *lenmodel;  // per record: loop (low 16 bits) | move << 16 (int16 each)
+    const uint32_t *gentle;    // [kP7Loops] records whose loop score is at least -v: the
+                               // first ones, as |loop| falls with the length
     int32_t nseq;
     uint32_t pad_off;
     int16_t *score;
@@ -230,6 +232,7 @@ hipError_t launch_select(const SeqRec *seqs, int64_t nseq, const void *score,
 
 constexpr int kMaxP7G = 64;
 constexpr int kP7Parts = 16;                 // record queues of a P7 call
+constexpr int kP7Loops = 65;                 // |loop score| of a sequence with residues: 0..64
 // P7 calls' workspace: aux words at 0, the queues of both kernels from
 // kWsCounterBytes, their LDS images after them, the pending list in the
 // window area.

@@ -73,6 +73,7 @@ constexpr int kAuxTransOk = 1;    // transitions and tBM within the cost form's 
 constexpr int kAuxMinII = 2;      // smallest I->I cost over the nodes
 constexpr int kAuxRise = 3;       // largest sum of a run of D~->D~ scores (0 if none is above)
 constexpr int kAuxPend = 4;       // records the cost form leaves to p7_kernel
+constexpr int kAuxFast = 5;       // the call's first records, which the cost form takes
 constexpr int kAuxEmisOk = 8;     // per emission row: no score above kP7Bias
 static_assert((kAuxEmisOk + kDegenRows) * 4 <= (int)kWsCounterBytes, "aux words fit");
 
@@ -83,6 +84,13 @@ __device__ __forceinline__ bool p7_profile_fast(const P7Args &a) {
     bool bad = a.aux[kAuxTransOk] == 0;
     if (lane < a.rows) bad = bad || a.aux[kAuxEmisOk + lane] == 0;
     return !__any(bad);
+}
+
+// Records of the call: the whole database's, or those that a selection pass
+// left in sel[0 .. *nsel) (a device count, known only here; never more than the
+// database holds).
+__device__ __forceinline__ int p7_records(const P7Args &a) {
+    return a.sel ? min(max(*a.nsel, 0), a.nseq) : a.nseq;
 }
 
 // Record queues.  Records come from queues (counters the prep kernel
@@ -264,7 +272,26 @@ __global__ void __launch_bounds__(256) p7_prep_kernel(P7Args a, int image_blocks
             a.aux[kAuxTransOk] = bad ? 0 : 1;
             a.aux[kAuxMinII] = minii;
             a.aux[kAuxRise] = red[3][0];
-            a.aux[kAuxPend] = 0;
+        }
+        // The records that the cost form takes: those whose |loop| is at most the
+        // smallest I->I cost, the first ones of the processing order; of a
+        // selection (longest first, as hmsv_select writes it), those before
+        // the first position past them, found with 256 probes at a time.  In
+        // any other order some of the rest are before it: the cost form's
+        // kernel sends those back one by one.
+        const int n = p7_records(a);
+        const int past = (int)a.gentle[min(max(minii, 0), kP7Loops - 1)];
+        int lo = a.sel ? 0 : min(past, n), hi = a.sel ? n : lo;
+        while (lo < hi) {
+            const int step = (hi - lo + 255) / 256;
+            const int r = lo + (int)threadIdx.x * step;
+            const int k = __syncthreads_count(r < hi && a.sel[r] < past);
+            hi = min(hi, lo + k * step);
+            if (k > 0) lo += (k - 1) * step + 1;
+        }
+        if (threadIdx.x == 0) {
+            a.aux[kAuxFast] = lo;
+            a.aux[kAuxPend] = n - lo;             // the rest, listed first
         }
         if (threadIdx.x < kP7Parts) {                       // the record queues
             a.queue[threadIdx.x * 32] = 0u;
@@ -310,13 +337,11 @@ template <int G, int Q, int THREADS>
 __global__ void __launch_bounds__(THREADS) p7_kernel(P7Args a) {
     using Lay = Layout<G, Q, kP7Rows>;
     constexpr int RS = Lay::RS;
-    // Records: the whole database (processing positions 0..nseq-1), or the
-    // positions a selection pass left in sel[0 .. *nsel) (a device count,
-    // known only here; never more than the database holds); or, where the cost
-    // form holds for the profile, the few that its kernel left.
+    // Records: all of the call's, or, where the cost form holds for the profile,
+    // the ones its kernel listed.
     const bool rest = p7_profile_fast(a);
     const int32_t *sel = rest ? a.pend : a.sel;
-    const int nseq = rest ? a.aux[kAuxPend] : sel ? min(*a.nsel, a.nseq) : a.nseq;
+    const int nseq = rest ? a.aux[kAuxPend] : p7_records(a);
     if (rest) {
         // the first blocks are enough (at least one per queue)
         const int per = (int)(blockDim.x / G);
