@@ -474,16 +474,20 @@ filter_kernel(KArgs a) {
     // a large part of the mean work per group, so that what is fixed adds up to
     // about the same for each.  (All in the order of the first ones: SSV at
     // M = 30, 500,000 sequences 222 us, in this order 210; M = 64 397 and 365.)
+    // With nlong < 0 all are in the order of the first ones after all.
     constexpr int kNone = 0x7fffffff;
-    const int nlong = a.nlong;
+    const bool inorder = a.nlong < 0;
+    const int nlong = inorder ? 0 : a.nlong;
     const int i2 = 2 * ngroups - nlong;           // end of the second ones in order
     const int i3 = i2 + ngroups - nlong;          // and of the third ones
     auto second = [&](int g) -> int {
-        const int r = g < nlong ? nv - 1 - g : 2 * ngroups - 1 - g;
+        const int r = inorder ? ngroups + g : g < nlong ? nv - 1 - g : 2 * ngroups - 1 - g;
         return g < nlong ? (r >= i2 ? r : kNone) : (r < nv ? r : kNone);
     };
     auto third = [&](int g) -> int {
-        const int r = g < nlong ? nv - 1 - nlong - g : i2 + ngroups - 1 - g;
+        const int r = inorder     ? i2 + g
+                      : g < nlong ? nv - 1 - nlong - g
+                                  : i2 + ngroups - 1 - g;
         return g < nlong ? (r >= i3 ? r : kNone) : (r < nv - nlong ? r : kNone);
     };
     // Claims come from a.parts counters, one or kQueues, each on its own

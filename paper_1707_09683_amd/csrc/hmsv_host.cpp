@@ -493,18 +493,30 @@ void plan_split(const hmsv_db *db, int64_t first, int64_t count, const KernelEnt
     constexpr double kCyclesPerNs = 2.35, kClaimNs = 3.0;
     a.parts = c.cycles >= kClaimNs * kCyclesPerNs * (double)share * (double)nrec ? 1 : kQueues;
     // Groups that start on a record of more than half the mean work go on with
-    // the shortest records.  With six or more
-    // records per group all do: wavefronts advance unequally (the oldest of a
-    // SIMD first), and the claims that even this out should have the long
-    // records.  M = 400, 500,000 sequences (15 per group): 1784 us by the first
-    // rule, 1709 by the second; M = 1000, 100,000 (12): 877 and 846; M = 128,
-    // 250,000 (4): 374 and 388.
+    // the shortest records.  With 3.5 or more records per group all do: wavefronts
+    // advance unequally (the oldest of a SIMD first), and the claims that even
+    // this out should have the long records.  M = 400, 500,000 sequences (7.6 per
+    // group): 1784 us by the first rule, 1709 by the second; M = 100, 500,000
+    // (3.9): 517 and 490; M = 300, 250,000 (5.1): 705 and 679; M = 60, 500,000
+    // (3.1): 337 and 346.
+    // With 1.75 to 3.5 records of even lengths per group, records in order: equal
+    // sums are no help there, as the oldest wavefronts then end first and leave
+    // the youngest alone on their SIMDs.  50 to 500 residues, 167,000 sequences,
+    // M = 164 (2.04 per group): 266 us by the first rule, 211 in order; M = 400
+    // (2.55): 522 and 487; M = 700, 60,000 (2.9): 316 and 299; but M = 100 (1.27)
+    // 133 and 145, and lognormal lengths, M = 100, 250,000 (2.01), 274 and 292.
     const int64_t groups = *blocks * per_block;
-    const int64_t half = (r.upto(count) + (int64_t)(a.nsegs - a.nsplit) * a.warm) / groups / 2;
+    const int64_t rows = r.upto(count) + (int64_t)(a.nsegs - a.nsplit) * a.warm;
+    const int64_t half = rows / groups / 2;
     int64_t nl = r.above(half) - a.nsplit;
     if (nl < 0) nl = 0;
     if (a.seg_rows + a.warm > half) nl += a.nsegs;
-    a.nlong = (int32_t)(nrec >= 6 * groups ? groups : std::min(nl, groups));
+    const int64_t longest = std::max<int64_t>(a.nsegs > 0 ? a.seg_rows + a.warm : 0,
+                                              a.nsplit < count ? r.rows(a.nsplit) : 0);
+    const bool even = longest * nrec <= 2 * rows;
+    if (2 * nrec >= 7 * groups) nl = groups;
+    else if (even && 4 * nrec >= 7 * groups) nl = -1;
+    a.nlong = (int32_t)std::min(nl, groups);
 }
 
 hmsv_status score_common(int is_msv, const hmsv_profile *prof, const hmsv_db *db,

@@ -84,7 +84,8 @@ struct KArgs {
     int32_t warm;          // rows before a segment (multiple of 16, >= M - 1)
     int32_t parts;         // claim counters in use, 1..kQueues
     int32_t nlong;         // groups whose first record is a large part of the mean
-                           // work per group (at most the grid's groups)
+                           // work per group (at most the grid's groups); -1: each
+                           // group's first records in order
     // Split sequence t has v = ceil(rows / seg_rows) segments, which take
     // records p .. p + v - 1.  Records are longest first, so v only falls
     // with t: bin b covers t >= bin_t[b] with v = bin_v[b] and

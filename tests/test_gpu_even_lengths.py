@@ -1,0 +1,84 @@
+"""Filter calls on sequences of even lengths, 1.75 to 3.5 records per lane group:
+each group takes its first records in order.  Every sequence is scored once
+and exactly at the edges of that range, and such a call is not slower for the
+number of its groups."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import quant as oq
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+M = 40
+
+
+@pytest.fixture(scope="module")
+def hm():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1707_09683_amd as m
+    return m
+
+
+def database(rng, lengths, emis):
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    res = rng.integers(0, 20, int(off[-1])).astype(np.uint8)
+    synth.implant(rng, res, off, [emis], 0.1)
+    return res, off
+
+
+@pytest.mark.parametrize("lengths", ["equal", "even", "one long"])
+@pytest.mark.parametrize("G,blocks", [(1, 1), (8, 3), (16, 17)])
+@pytest.mark.parametrize("filt", ["msv", "ssv"])
+def test_records_per_group(hm, filt, G, blocks, lengths):
+    rng = np.random.default_rng(5)
+    emis = synth.sample_emissions(rng, M)
+    prof = hm.Profile.from_emissions(emis, synth.BG)
+    plan = hm.make_plan(G, -(-(M + 1) // (2 * G)), waves_per_block=4, blocks=blocks)
+    N = blocks * 4 * (64 // G)
+    for n in sorted({(7 * N - 1) // 4, -(-7 * N // 4), 2 * N - 1, 2 * N, 2 * N + 1, 3 * N - 1, 3 * N,
+                     3 * N + 1, (7 * N - 1) // 2, -(-7 * N // 2)}):
+        L = np.full(n, 33) if lengths == "equal" else rng.integers(30, 56, n)
+        if lengths == "one long":
+            L[n // 3] = 150
+        res, off = database(rng, L, emis)
+        exp = oracle.score_db(filt, oq.quantize(emis, synth.BG), res, off)
+        gdb = hm.Database(res, off)
+        sdt = torch.uint8 if filt == "msv" else torch.int8
+        s = torch.full((n,), 99, dtype=sdt, device="cuda")
+        f = torch.full((n,), 99, dtype=torch.uint8, device="cuda")
+        print(f"case {filt} G={G} blocks={blocks} n={n} {lengths}", flush=True)
+        (hm.msv_score if filt == "msv" else hm.ssv_score)(prof, gdb, s, f, plan=plan)
+        torch.cuda.synchronize()
+        gdb.close()
+        bad = np.nonzero((s.cpu().numpy() != exp[0]) | (f.cpu().numpy() != exp[1]))[0]
+        assert bad.size == 0, (n, bad[:5])
+
+
+def test_time(hm):
+    """2.04 records per group (blocks of four wavefronts, five of them on a CU)
+    take no more than 1.7 (blocks of eight, three), which share the rest: 11%
+    of one record's rows more, and as much again for the spread of the runs."""
+    rng = np.random.default_rng(6)
+    m, n = 164, 167_000
+    L = rng.integers(50, 501, n)
+    off = np.concatenate([[0], np.cumsum(L)]).astype(np.int64)
+    gdb = hm.Database(rng.integers(0, 20, int(off[-1])).astype(np.uint8), off)
+    prof = hm.Profile.from_emissions(synth.sample_emissions(rng, m), synth.BG)
+    ws = hm.new_workspace("cuda", n)
+    best = {}
+    for w in (4, 8) * 4:
+        plan = hm.make_plan(4, 21, waves_per_block=w)
+        print(f"case even lengths time {w}", flush=True)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        hm.ssv_score(prof, gdb, workspace=ws, plan=plan)
+        a.record()
+        for _ in range(10):
+            hm.ssv_score(prof, gdb, workspace=ws, plan=plan)
+        b.record()
+        torch.cuda.synchronize()
+        best[w] = min(best.get(w, 1e9), a.elapsed_time(b))
+    assert best[4] < 1.15 * best[8], best
