@@ -211,7 +211,8 @@ int32_t hmsv_db_table_rows(const hmsv_db *db);
  * -inf node).  64/G sequences share a wavefront (the paper's
  * multi-sequence alignment, Sec. 3.1 tier 4).  waves_per_block (1..8, or
  * 1..16 for G >= 32 or Q > 32) wavefronts share one LDS copy of the profile;
- * blocks = 0 picks a persistent grid of the resident maximum. */
+ * blocks = 0 picks a persistent grid of the resident maximum; MSV and SSV
+ * calls launch no more blocks than their records fill. */
 typedef struct {
     int32_t G;
     int32_t Q;

@@ -483,8 +483,9 @@ void plan_split(const hmsv_db *db, int64_t first, int64_t count, const KernelEnt
         break;
     }
     const int64_t nrec = count - a.nsplit + a.nsegs;
-    if (plan.blocks == 0)
-        *blocks = (int)std::min<int64_t>(most, (nrec + per_block - 1) / per_block);
+    // (a plan's own grid too: the kernels number three records per lane group in
+    // 32 bits, and groups past the records have nothing to do)
+    *blocks = (int)std::min<int64_t>(most, (nrec + per_block - 1) / per_block);
     // One counter serves a claim every 2 to 4 ns; with sixteen, one for each
     // 1/16 of the blocks, some blocks run out before others.  M = 400 on 500,000
     // sequences (3.4 ns per record) 1705 us with sixteen, 1680 with one;
@@ -570,6 +571,8 @@ hmsv_status score_common(int is_msv, const hmsv_profile *prof, const hmsv_db *db
 
     int blocks = grid_blocks(e, plan, count, db->table_rows);
     if (blocks <= 0) return HMSV_EDEVICE;
+    // more work items than a launch may have
+    if ((int64_t)blocks * plan.waves_per_block * 64 > (int64_t)UINT32_MAX) return HMSV_EDEVICE;
     plan_split(db, first, count, e, plan, prof->M, &blocks, a, share);
     // MSV: a second kernel rescores the windows the first one stored
     ExactLaunchFn xf = nullptr;

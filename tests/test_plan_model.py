@@ -1,0 +1,48 @@
+"""The host code that chooses a call's plan, cuts and grid, run without a GPU
+(tests/host/model_driver.cpp)."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1707_09683_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    """Answers of the driver to a list of commands."""
+    hipcc = "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path_factory.mktemp("driver") / "model_driver")
+    p = subprocess.run([hipcc, "-O1", "-std=c++20", "--offload-arch=gfx950",
+                        "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                        "-I", CSRC, "-I", os.path.join(ROOT, "include"), "-w", "-x", "hip",
+                        os.path.join(ROOT, "tests", "host", "model_driver.cpp"),
+                        os.path.join(CSRC, "select.hip"), "-o", exe],
+                       capture_output=True, text=True, timeout=600)
+    assert p.returncode == 0, p.stderr[-4000:]
+
+    def ask(commands):
+        r = subprocess.run([exe], input="\n".join(commands) + "\n", capture_output=True, text=True,
+                           timeout=300)
+        assert r.returncode == 0, r.stderr[-2000:]
+        out = r.stdout.strip().split("\n")
+        assert len(out) == len(commands) and not any(o.startswith("?") for o in out), out[:3]
+        return out
+    return ask
+
+
+@pytest.mark.parametrize("G,w", [(1, 8), (1, 4), (2, 8), (64, 16)])
+def test_grid_of_a_plan_holds_no_more_groups_than_records(driver, G, w):
+    """A plan's own grid beyond its call's records (2^31 lane groups among
+    them): the kernels number three records per lane group in 32 bits."""
+    Q = -(-41 // (2 * G))
+    per_block = w * (64 // G)
+    for n, blocks in ((1, 1), (1, 5), (1000, 3), (1000, 1 << 22), (1000, (1 << 31) - 1),
+                      (70000, 100000)):
+        got, nsegs, nlong = map(int, driver([f"grid {n} 50 40 {G} {Q} {w} {blocks}"])[0].split())
+        assert nsegs == 0
+        assert got == min(blocks, -(-n // per_block))
+        assert 3 * got * per_block < 1 << 31 and nlong <= got * per_block
