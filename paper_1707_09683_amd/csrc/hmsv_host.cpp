@@ -261,11 +261,17 @@ bool tuned_plan(int kind, int M, hmsv_plan *plan) {
 //  * with n wavefronts on a SIMD, 0.65 / n^2 more (what they don't hide);
 //  * a sequence's end stops its wavefront for 105 cycles per wavefront on the
 //    SIMD.
-constexpr double kSimds = 1024.0;            // 256 CUs x 4
+constexpr int kCus = 256;                    // where no device says otherwise
 double row_issue(int G, int Q) {
     return (6.3 * Q + 13.5) * (Q > 32 ? 1.11 : 1.0) * (G == 64 ? 1.15 : 1.0);
 }
 double row_alone(int G, int Q) { return (31.0 + 10.5 * Q) * (G == 64 ? 1.15 : 1.0); }
+
+// Compute units for the model of a call on the current device.
+int model_cus() {
+    const int n = device_cus();
+    return n > 0 ? n : kCus;
+}
 
 // Rows of records [0, t) of a range, and of record t.
 struct Range {
@@ -308,12 +314,14 @@ constexpr double kCutCycles = 9000.0, kSegCycles = 2.5;
 // taken as so many times the records: one's end is filled by the others
 // (1500 nodes and four shorter profiles on 20,000 sequences at once, cut as if
 // alone 817 us, so 737; eight of up to 1800 on 60,000 2770 and 2711).
-Cut choose_cut(const Range &r, int M, int G, int Q, int64_t ngroups, int share = 1) {
+// cus: compute units of the device (fewer on a partition of one).
+Cut choose_cut(const Range &r, int M, int G, int Q, int64_t ngroups, int cus, int share = 1) {
     const int64_t warm = ((M - 1) + 15) & ~15;
     const int64_t longest = r.rows(0);
     const double s = (double)share, total = s * (double)r.upto(r.count);
     const double issue = row_issue(G, Q), alone = row_alone(G, Q);
     const double batch = G == 1 ? 8.0 : G == 2 ? 4.0 : G == 4 ? 2.0 : 1.0;   // ends per stop
+    const double simds = 4.0 * (double)cus;
     const double mean0 = total / std::max(1.0, std::min((double)ngroups, s * (double)r.count));
     Cut best;
     for (int k = -1; k < 12; ++k) {
@@ -335,7 +343,7 @@ Cut choose_cut(const Range &r, int M, int G, int Q, int64_t ngroups, int share =
         const double rows = total + s * (double)(segs - ns) * (double)warm + 8.0 * nrec;
         const double n = std::min((double)ngroups, nrec);
         const double waves = std::max(1.0, n * G / 64.0);
-        const double per_simd = std::max(1.0, waves / kSimds);   // wavefronts per SIMD
+        const double per_simd = std::max(1.0, waves / simds);    // wavefronts per SIMD
         const double mean = rows / n;
         const double exposed = per_simd > 1.5 ? 1.0 + 0.65 / (per_simd * per_simd) : 1.0;
         c.cycles = mean * std::max(alone, issue * per_simd) * exposed +
@@ -380,7 +388,7 @@ int block_waves(int G, int Q, int rows) {
 // leave less room for another query's blocks (735, 610 and 164 nodes on
 // 167,000 sequences at once: 2074 us with them, 1865 without).
 hmsv_status resolve_plan(int is_msv, int M, int rows, const Range &r, const hmsv_plan *in,
-                         hmsv_plan *out, int share = 1) {
+                         hmsv_plan *out, int cus, int share = 1) {
     if (lds_bytes(kExactG, exact_q(M), rows) > (size_t)kLdsBytes) return HMSV_EUNSUPPORTED;
     if (in) {
         *out = *in;
@@ -406,13 +414,13 @@ hmsv_status resolve_plan(int is_msv, int M, int rows, const Range &r, const hmsv
         p.blocks = 0;
         double t = 0.0;
         if (r.count > 0) {
-            int64_t waves = 256 * resident_waves(G, p.Q, p.waves_per_block, rows);
+            int64_t waves = cus * resident_waves(G, p.Q, p.waves_per_block, rows);
             if (is_tuned && share == 1 && r.upto(r.count) < waves * (64 / G) * r.rows(0)) {
                 // the longest records set the end: see block_waves
                 p.waves_per_block = std::min(p.waves_per_block, block_waves(G, p.Q, rows));
-                waves = 256 * resident_waves(G, p.Q, p.waves_per_block, rows);
+                waves = cus * resident_waves(G, p.Q, p.waves_per_block, rows);
             }
-            t = choose_cut(r, M, G, p.Q, waves * (64 / G), share).cycles *
+            t = choose_cut(r, M, G, p.Q, waves * (64 / G), cus, share).cycles *
                 (is_tuned ? 0.95 : 1.0);
         } else if (!is_tuned) {
             t = (double)G;              // nothing to score: the tuned plan, or the narrowest
@@ -446,7 +454,7 @@ int grid_blocks(const KernelEntry *e, const hmsv_plan &plan, int64_t count, int 
 // blocks of its grid: segments may fill more lane groups than there are
 // sequences.
 void plan_split(const hmsv_db *db, int64_t first, int64_t count, const KernelEntry *e,
-                const hmsv_plan &plan, int M, int *blocks, KArgs &a, int share = 1) {
+                const hmsv_plan &plan, int M, int *blocks, KArgs &a, int cus, int share = 1) {
     a.nsplit = 0;
     a.nsegs = 0;
     a.nbins = 0;
@@ -457,7 +465,8 @@ void plan_split(const hmsv_db *db, int64_t first, int64_t count, const KernelEnt
     if (plan.blocks == 0) most = resident_blocks(e, plan.waves_per_block, db->table_rows);
     if (most < *blocks) most = *blocks;
     const Range r{db->cum_rows.data() + first, count};
-    const Cut c = count < 2 ? Cut{} : choose_cut(r, M, plan.G, plan.Q, (int64_t)most * per_block, share);
+    const Cut c = count < 2 ? Cut{}
+                            : choose_cut(r, M, plan.G, plan.Q, (int64_t)most * per_block, cus, share);
     int64_t T = c.seg, limit = c.limit;
     for (; T > 0 && T < (int64_t)kRowsLimit; T *= 2, limit *= 2) {
         const int64_t ns = r.above(limit);
@@ -537,7 +546,7 @@ hmsv_status score_common(int is_msv, const hmsv_profile *prof, const hmsv_db *db
     hmsv_plan plan;
     st = resolve_plan(is_msv, prof->M, db->table_rows,
                       Range{db->cum_rows.data() + (in_range ? first : 0), in_range ? count : 0},
-                      plan_in, &plan);
+                      plan_in, &plan, model_cus());
     if (st != HMSV_OK) return st;
     const KernelEntry *e = registry().find(is_msv, plan.G, plan.Q);
     if (!e) return HMSV_ENOKERNEL;
@@ -573,7 +582,7 @@ hmsv_status score_common(int is_msv, const hmsv_profile *prof, const hmsv_db *db
     if (blocks <= 0) return HMSV_EDEVICE;
     // more work items than a launch may have
     if ((int64_t)blocks * plan.waves_per_block * 64 > (int64_t)UINT32_MAX) return HMSV_EDEVICE;
-    plan_split(db, first, count, e, plan, prof->M, &blocks, a, share);
+    plan_split(db, first, count, e, plan, prof->M, &blocks, a, model_cus(), share);
     // MSV: a second kernel rescores the windows the first one stored
     ExactLaunchFn xf = nullptr;
     int cus = 0;
@@ -1015,7 +1024,7 @@ hmsv_status hmsv_db_default_plan(const hmsv_db *db, int32_t is_msv, int32_t M, h
     if (!db || !plan || M < 1) return HMSV_EINVAL;
     if (M > HMSV_MAX_M) return HMSV_EUNSUPPORTED;
     return resolve_plan(is_msv ? 1 : 0, M, db->table_rows, Range{db->cum_rows.data(), db->nseq},
-                        nullptr, plan);
+                        nullptr, plan, model_cus());
 }
 
 hmsv_status hmsv_default_plan(int32_t is_msv, int32_t M, hmsv_plan *plan) {
@@ -1096,7 +1105,8 @@ hmsv_status hmsv_split_info(const hmsv_db *db, int64_t first, int64_t count, int
     hmsv_plan plan;
     hmsv_status st = resolve_plan(
         is_msv ? 1 : 0, M, db->table_rows,
-        Range{db->cum_rows.data() + (in_range ? first : 0), in_range ? count : 0}, plan_in, &plan);
+        Range{db->cum_rows.data() + (in_range ? first : 0), in_range ? count : 0}, plan_in, &plan,
+        model_cus());
     if (st != HMSV_OK) return st;
     const KernelEntry *e = registry().find(is_msv ? 1 : 0, plan.G, plan.Q);
     if (!e) return HMSV_ENOKERNEL;
@@ -1106,7 +1116,7 @@ hmsv_status hmsv_split_info(const hmsv_db *db, int64_t first, int64_t count, int
     int blocks = grid_blocks(e, plan, count, db->table_rows);
     if (blocks <= 0) return HMSV_EDEVICE;
     KArgs a{};
-    plan_split(db, first, count, e, plan, M, &blocks, a);
+    plan_split(db, first, count, e, plan, M, &blocks, a, model_cus());
     *nsplit = a.nsplit;
     *nsegs = a.nsegs;
     *seg_rows = a.seg_rows;
@@ -1232,7 +1242,7 @@ namespace {
 // the LDS (Q > 6).  The longest record rules small databases, and the widest
 // groups run one fastest: M = 200 on 20,000 sequences 2070 us with 16 lanes (the
 // measured plan of large databases), 940 with 64; on 200,000 3300 and 5570.
-void p7_choose(const hmsv_db *db, int M, hmsv_plan *plan) {
+void p7_choose(const hmsv_db *db, int M, hmsv_plan *plan, int cus) {
     const hmsv_plan tuned = *plan;
     const double total = (double)db->cum_rows[(size_t)db->nseq], nseq = (double)db->nseq;
     const double longest = (double)db->cum_rows[1];
@@ -1253,7 +1263,7 @@ void p7_choose(const hmsv_db *db, int M, hmsv_plan *plan) {
         const int by_regs = p.Q == 1 ? 32 : p.Q == 2 ? 28 : p.Q <= 8 ? 20 : 16;
         const int by_lds = (int)((size_t)kLdsBytes / lds) * p.waves_per_block;
         const double resident = (double)std::max(p.waves_per_block, std::min(by_lds, by_regs));
-        const double a = G / 64.0 / kSimds *
+        const double a = G / 64.0 / (4.0 * (double)cus) *
                          (total * (41.0 * p.Q + 78.0) * (1.0 + 3.0 / resident) + nseq * 2000.0);
         const double b = longest * (71.0 * p.Q + 251.0) * (p.Q > 6 ? 1.27 : 1.0);
         const double t = std::pow(std::pow(a, 5.0) + std::pow(b, 5.0), 0.2);
@@ -1288,7 +1298,7 @@ hmsv_status p7_common(const hmsv_p7_profile *prof, const hmsv_db *db, const int3
     } else {
         hmsv_status st = hmsv_p7_default_plan(prof->M, &plan);
         if (st != HMSV_OK) return st;
-        if (db->nseq > 0) p7_choose(db, prof->M, &plan);
+        if (db->nseq > 0) p7_choose(db, prof->M, &plan, model_cus());
     }
     if (plan.G < 1 || plan.G > 64 || (64 % plan.G) != 0 || plan.Q < 1 ||
         plan_nodes(plan.G, plan.Q) < prof->M || plan.blocks < 0 ||
@@ -1394,7 +1404,7 @@ hmsv_status hmsv_batch_create(const hmsv_query *queries, int32_t nq, const hmsv_
             if (queries[k].workspace == q.workspace) return HMSV_EINVAL;
         st = resolve_plan(q.is_msv ? 1 : 0, q.prof.M, db->table_rows,
                           Range{db->cum_rows.data(), db->nseq},
-                          q.plan.G == 0 ? nullptr : &q.plan, &plans[i],
+                          q.plan.G == 0 ? nullptr : &q.plan, &plans[i], model_cus(),
                           std::min(branches, nq));
         if (st != HMSV_OK) return st;
         if (!registry().find(q.is_msv ? 1 : 0, plans[i].G, plans[i].Q)) return HMSV_ENOKERNEL;

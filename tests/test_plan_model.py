@@ -46,3 +46,21 @@ def test_grid_of_a_plan_holds_no_more_groups_than_records(driver, G, w):
         assert nsegs == 0
         assert got == min(blocks, -(-n // per_block))
         assert 3 * got * per_block < 1 << 31 and nlong <= got * per_block
+
+
+@pytest.mark.parametrize("cus", [32, 64, 128])
+@pytest.mark.parametrize("kind", [0, 1, 2], ids=["ssv", "msv", "p7"])
+def test_part_of_a_gpu_gets_its_own_plan(driver, kind, cus):
+    """A partition of the GPU on a database runs as the whole GPU does on as
+    many copies of it as there are such partitions: the same width and the same
+    cut (the longest record is the same, each SIMD's share too)."""
+    k = 256 // cus
+    ask = [(M, n) for M in (30, 100, 400, 1000, 2400) for n in (50, 500, 5000)]
+    part = driver([f"plan {kind} {M} {cus} {n} 1" for M, n in ask])
+    whole = driver([f"plan {kind} {M} 256 {n} {k}" for M, n in ask])
+    same = sum(a.split()[0] == b.split()[0] for a, b in zip(part, whole))
+    # a segment's record and the launch cost the same on fewer units, so a plan on
+    # the edge may differ
+    assert same >= len(ask) - 2, list(zip(ask, part, whole))
+    # and it is not the whole GPU's plan for that database throughout
+    assert part != driver([f"plan {kind} {M} 256 {n} 1" for M, n in ask])
