@@ -234,25 +234,29 @@ def resources(jobs: int | None = None) -> str:
             for m in rx.finditer(err):
                 k, v = m.group(1), m.group(2)
                 if k == "Function Name":
-                    mm = re.search(r"p7_kernelILi\d+ELi\d+ELi(\d+)E", v)
-                    cur = (G, Q, int(mm.group(1))) if mm else None
+                    mm = re.search(r"(p7_fast_kernel|p7_kernel)ILi\d+ELi\d+ELi(\d+)E", v)
+                    cur = (mm.group(1), G, Q, int(mm.group(2))) if mm else None
                     if cur:
                         p7_use[cur] = {}
                 elif cur:
                     p7_use[cur][k] = int(v)
-    lines += ["", "P7Viterbi (`p7_kernel<G, Q, threads>`, default plans at the measured lengths; "
-              "blocks of 16 wavefronts are 1024-thread kernels):",
-              "", "| M-bins | G | Q | waves/block | VGPRs | SGPRs | scratch B/lane | "
+    lines += ["", "P7Viterbi (`p7_fast_kernel<G, Q, threads>`, the cost form, and "
+              "`p7_kernel<G, Q, threads>`, the general kernel; default plans at the measured "
+              "lengths; blocks of 16 wavefronts are 1024-thread kernels):",
+              "", "| kernel | M-bins | G | Q | waves/block | VGPRs | SGPRs | scratch B/lane | "
               "waves/SIMD (VGPRs) | LDS KiB/block | waves/SIMD (launch) |",
-              "|---|---|---|---|---|---|---|---|---|---|"]
-    for (G, Q, wpb), Ms in sorted(p7_plans.items(), key=lambda t: min(t[1])):
-        u = p7_use.get((G, Q, 1024 if wpb > 8 else 512), {})
-        lds = p7_lds_bytes(G, Q)
-        occ_v = u.get("Occupancy [waves/SIMD]", 0)
-        blocks = min(160 * 1024 // lds, (4 * occ_v) // wpb) if lds else 0
-        lines.append(f"| {','.join(map(str, Ms))} | {G} | {Q} | {wpb} | {u.get('VGPRs')} | "
-                     f"{u.get('TotalSGPRs')} | {u.get('ScratchSize [bytes/lane]')} | {occ_v} | "
-                     f"{lds / 1024:.1f} | {blocks * wpb / 4:g} |")
+              "|---|---|---|---|---|---|---|---|---|---|---|"]
+    for kernel in ("p7_fast_kernel", "p7_kernel"):
+        for (G, Q, wpb), Ms in sorted(p7_plans.items(), key=lambda t: min(t[1])):
+            u = p7_use.get((kernel, G, Q, 1024 if wpb > 8 else 512), {})
+            # the cost form has five rows of transitions to the general kernel's seven
+            lds = p7_lds_bytes(G, Q) * (26 if kernel == "p7_fast_kernel" else 28) // 28
+            occ_v = u.get("Occupancy [waves/SIMD]", 0)
+            blocks = min(160 * 1024 // lds, (4 * occ_v) // wpb) if lds else 0
+            lines.append(f"| {kernel} | {','.join(map(str, Ms))} | {G} | {Q} | {wpb} | "
+                         f"{u.get('VGPRs')} | {u.get('TotalSGPRs')} | "
+                         f"{u.get('ScratchSize [bytes/lane]')} | {occ_v} | "
+                         f"{lds / 1024:.1f} | {blocks * wpb / 4:g} |")
     return "\n".join(lines)
 
 

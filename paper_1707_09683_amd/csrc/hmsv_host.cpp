@@ -1182,8 +1182,7 @@ constexpr P7Tuned kP7Tuned[] = {
     {2200, 64, 16}, {2400, 64, 16}, {2815, 64, 8},
 };
 
-// Largest block (in wavefronts) of a P7 plan: 16 for the 64-lane kernels
-// that fit a 1024-thread block's 128 VGPRs without spilling, else 8.
+// Largest block (in wavefronts) of a P7 plan (kP7MaxWaves in p7_fast.hpp).
 int p7_max_waves(int G, int Q) { return (G == 64 && (Q <= 18 || Q == 20)) ? 16 : 8; }
 
 hmsv_status hmsv_p7_default_plan(int32_t M, hmsv_plan *plan) {
@@ -1208,8 +1207,8 @@ hmsv_status hmsv_p7_default_plan(int32_t M, hmsv_plan *plan) {
     const int G0 = kP7Tuned[best].G;
     int Q0 = (M + 1 + 2 * G0 - 1) / (2 * G0);
     // 64 lanes of 19 registers run as 20 (one more slot per register): the
-    // 20-register kernel fits blocks of 16 wavefronts, the 19 one does not
-    // (measured at M = 2400: 4.05 against 3.25 TCUPS)
+    // 20-register kernel is built for blocks of 16 wavefronts, the 19 one is not
+    // (M = 2400 on 100,000 sequences 13.9 ms with 16, 17.4 with 19 registers and 8)
     if (G0 == 64 && Q0 == 19 && kP7Tuned[best].wpb > 8) Q0 = 20;
     if (fits(G0, Q0)) {
         plan->G = G0;
