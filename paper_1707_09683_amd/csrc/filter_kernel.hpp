@@ -1117,11 +1117,9 @@ __global__ void __launch_bounds__(THREADS) exact_kernel(KArgs a) {
 }
 
 // Block sizes: up to 8 wavefronts, or up to 16 for groups of 32 and 64 lanes
-// (their large LDS tables allow one block per CU, so a 16-wavefront block is
-// the only way to four wavefronts per SIMD).  Each size is its own kernel:
+// and for more than 32 registers (their large LDS tables allow one block per
+// CU, so a 16-wavefront block is the only way to four wavefronts per SIMD).  Each size is its own kernel:
 // the compiler budgets registers for the block size it is told.
-template <int G>
-constexpr int kMaxWaves = G >= 32 ? 16 : 8;
 template <int G, int Q>
 constexpr int kMaxWavesQ = (G >= 32 || Q > 32) ? 16 : 8;
 
