@@ -1336,6 +1336,7 @@ hmsv_status p7_common(const hmsv_p7_profile *prof, const hmsv_db *db, const int3
     a.flag = flags;
     a.image = (uint32_t *)((char *)workspace + kWsP7ImageOff);
     a.fimage = (uint32_t *)((char *)workspace + kWsP7FImageOff);
+    a.rise = (int32_t *)((char *)workspace + kWsP7RiseOff);
     a.queue = (uint32_t *)((char *)workspace + kWsP7QueueOff);
     a.fqueue = (uint32_t *)((char *)workspace + kWsP7FQueueOff);
     a.pend = (int32_t *)((char *)workspace + kWsWinOff);

@@ -213,6 +213,8 @@ struct P7Args {
     uint8_t *flag;
     uint32_t *image;       // the LDS image (workspace)
     uint32_t *fimage;      // the cost form's LDS image (workspace)
+    int32_t *rise;         // [kP7MaxSlots] per slot, what a run of D~->D~ scores from it on
+                           // adds at most (workspace)
     int32_t *aux;          // workspace words kAux..: the profile's bounds (prep kernel)
     uint32_t *queue;       // kP7Parts record queues, 128 bytes apart (zeroed by the
     uint32_t *fqueue;      // prep kernel); the cost form's kernel has its own
@@ -235,13 +237,15 @@ constexpr int kMaxP7G = 64;
 constexpr int kP7Parts = 16;                 // record queues of a P7 call
 constexpr int kP7Loops = 65;                 // |loop score| of a sequence with residues: 0..64
 // P7 calls' workspace: aux words at 0, the queues of both kernels from
-// kWsCounterBytes, their LDS images after them, the pending list in the
-// window area.
+// kWsCounterBytes, their LDS images after them, then the rise of each slot; the
+// pending list in the window area.
 constexpr size_t kWsP7QueueOff = kWsCounterBytes;
 constexpr size_t kWsP7FQueueOff = kWsP7QueueOff + (size_t)kP7Parts * 128;
 constexpr size_t kWsP7ImageOff = kWsP7FQueueOff + (size_t)kP7Parts * 128;
 constexpr size_t kWsP7FImageOff = kWsP7ImageOff + 160 * 1024;
-static_assert(kWsP7FImageOff + 160 * 1024 <= kWsWinOff, "P7 images within the workspace");
+constexpr size_t kWsP7RiseOff = kWsP7FImageOff + 160 * 1024;
+constexpr int kP7MaxSlots = 2816;            // 2 G Q of the widest plan
+static_assert(kWsP7RiseOff + kP7MaxSlots * 4 <= kWsWinOff, "P7 tables within the workspace");
 // Blocks of a P7 call's two kernels.
 struct P7Blocks {
     int general;

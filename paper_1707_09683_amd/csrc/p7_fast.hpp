@@ -98,11 +98,12 @@ __global__ void __launch_bounds__(THREADS) p7_fast_kernel(P7Args a) {
     }
     __syncthreads();
     const int minii = a.aux[kAuxMinII];
-    const uint32_t rise = splat_u(a.aux[kAuxRise]);
 
     const int lane = threadIdx.x & 63;
     const int j = lane % G;
     const bool gstart = j == 0;
+    // of the first slots of the lane's two elements
+    const uint32_t rise = (uint32_t)a.rise[2 * j * Q] | ((uint32_t)a.rise[(2 * j + 1) * Q] << 16);
     const uint32_t *T[3] = {lds + Lay::lane_off(lane, 4),
                             lds + Lay::OFF2 + Lay::lane_off(lane, 2),
                             lds + Lay::OFF1 + Lay::lane_off(lane, 1)};
@@ -352,8 +353,10 @@ __global__ void __launch_bounds__(THREADS) p7_fast_kernel(P7Args a) {
                 // ---- D~ within each element, ascending ---------------------
                 // (from the new M; slot 0 takes the previous element's last M
                 // here and its last D~ below).  Values up to F - rise reach no
-                // cell above F (rise: the most any run of D~->D~ scores adds up
-                // to), so slot 0 may be raised to that.
+                // cell above F (rise: the most that a run of D~->D~ scores from
+                // that slot on adds up to), so slot 0 may be raised to that.
+                // (With the largest rise of the profile for all: D->D of 0.9
+                // throughout, M = 60 on 20,000 sequences 3.88 ms.)
                 sM = shift_in(M[Q - 1]);
                 const uint32_t thr = usub(F, rise);
                 uint32_t dd0 = 0u;

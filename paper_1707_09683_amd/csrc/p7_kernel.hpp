@@ -71,7 +71,6 @@ static_assert(kP7Base + 32 + 720 + kP7MaxTbm < 0x7c00, "u stays a finite fp16 pa
 constexpr int kAuxMaxDm = 0;      // max over nodes of D->M
 constexpr int kAuxTransOk = 1;    // transitions and tBM within the cost form's bounds
 constexpr int kAuxMinII = 2;      // smallest I->I cost over the nodes
-constexpr int kAuxRise = 3;       // largest sum of a run of D~->D~ scores (0 if none is above)
 constexpr int kAuxPend = 4;       // records the cost form leaves to p7_kernel
 constexpr int kAuxFast = 5;       // the call's first records, which the cost form takes
 constexpr int kAuxEmisOk = 8;     // per emission row: no score above kP7Bias
@@ -205,9 +204,9 @@ __global__ void __launch_bounds__(256) p7_prep_kernel(P7Args a, int image_blocks
         return;
     }
     if ((int)blockIdx.x == check0) {
-        // the transitions: max of D->M, smallest I->I cost, the largest sum of
-        // a run of D~->D~ scores, and whether all are within the bounds
-        __shared__ int red[4][256];
+        // the transitions: max of D->M, smallest I->I cost, the rise of each
+        // slot, and whether all are within the bounds
+        __shared__ int red[2][256];
         auto top = [&](int t) {                   // red[t][0] = the maximum
             __syncthreads();
             for (int h = 128; h > 0; h >>= 1) {
@@ -232,46 +231,51 @@ __global__ void __launch_bounds__(256) p7_prep_kernel(P7Args a, int image_blocks
         red[1][threadIdx.x] = -mii;
         bad = __syncthreads_or(bad);
         const int maxdm = top(0), minii = -top(1);
-        // The largest sum of a run of D~->D~ scores (at least 0, the empty one).
-        // Each thread takes a run of neighbouring slots; neighbours are then
-        // joined two by two from {sum, largest prefix, largest suffix, largest
-        // run}.  A -inf score needs no case of its own: runs between them add
-        // at most the range of D->M, less than it takes.  (From every slot
-        // forward instead, one after the other, M = 2400 with D->D of 0 took 12
-        // ms a call.)
+        // The rise of slot s: the largest sum of D~->D~ scores from it on (at
+        // least 0, none), rise(s) = max(0, score into s + 1 + rise(s + 1)).  Each
+        // thread takes neighbouring slots; what they make of the rise behind them
+        // is max(own, sum + it), composed over the threads behind in log2(256)
+        // steps.  A -inf score needs no case of its own: runs between them add
+        // at most the range of D->M, less than it takes.  (A walk from every
+        // slot instead, M = 2400 with D->D of 0: 12 ms a call.)
         {
-            const int per = (a.M + 255) / 256;
-            const int s0 = 1 + (int)threadIdx.x * per;
-            int sum = 0, pre = 0, suf = 0, run = 0;
-            for (int s = s0; s < s0 + per && s <= a.M; ++s) {
-                const int d = (short)p7_slot_cost(a, a.rows + kFDD, s);
-                sum += d;
-                pre = sum > pre ? sum : pre;
-                suf = suf + d > 0 ? suf + d : 0;
-                run = suf > run ? suf : run;
+            constexpr int slots = 2 * G * Q, per = (slots + 255) / 256;
+            const int s0 = (int)threadIdx.x * per;
+            int sc[per], own = 0, sum = 0;
+#pragma unroll
+            for (int i = per - 1; i >= 0; --i) {
+                const int s = s0 + i;             // score into slot s + 1
+                sc[i] = s + 1 < slots ? (short)p7_slot_cost(a, a.rows + kFDD, s + 1) : kP7Neg;
+                own = max(0, own + sc[i]);
+                sum += sc[i];
             }
             __syncthreads();
-            red[0][threadIdx.x] = sum;
-            red[1][threadIdx.x] = pre;
-            red[2][threadIdx.x] = suf;
-            red[3][threadIdx.x] = run;
+            red[0][threadIdx.x] = own;
+            red[1][threadIdx.x] = sum;
+            __syncthreads();
             for (int h = 1; h < 256; h *= 2) {
+                const int at = (int)threadIdx.x + h;
+                const int o = at < 256 ? red[0][at] : 0, u = at < 256 ? red[1][at] : 0;
                 __syncthreads();
-                if (threadIdx.x % (2 * h) == 0) {
-                    const int l = (int)threadIdx.x, r = l + h;
-                    const int across = red[2][l] + red[1][r];
-                    red[3][l] = max(max(red[3][l], red[3][r]), across);
-                    red[1][l] = max(red[1][l], red[0][l] + red[1][r]);
-                    red[2][l] = max(red[2][r], red[2][l] + red[0][r]);
-                    red[0][l] += red[0][r];
+                if (at < 256) {
+                    own = max(own, sum + o);
+                    sum += u;
+                    red[0][threadIdx.x] = own;
+                    red[1][threadIdx.x] = sum;
                 }
+                __syncthreads();
+            }
+            int r = (int)threadIdx.x < 255 ? red[0][threadIdx.x + 1] : 0;
+#pragma unroll
+            for (int i = per - 1; i >= 0; --i) {
+                r = max(0, sc[i] + r);
+                if (s0 + i < slots) a.rise[s0 + i] = r;
             }
         }
         if (threadIdx.x == 0) {
             a.aux[kAuxMaxDm] = maxdm;
             a.aux[kAuxTransOk] = bad ? 0 : 1;
             a.aux[kAuxMinII] = minii;
-            a.aux[kAuxRise] = red[3][0];
         }
         // The records that the cost form takes: those whose |loop| is at most the
         // smallest I->I cost, the first ones of the processing order; of a

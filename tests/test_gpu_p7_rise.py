@@ -1,6 +1,6 @@
-"""The largest sum of a run of D~->D~ scores (csrc/p7_kernel.hpp, prep kernel):
-the value that the cost form uses, and that finding it takes a call no longer
-on profiles whose runs never end."""
+"""The rise of each slot, the largest sum of D~->D~ scores from it on
+(csrc/p7_kernel.hpp, prep kernel): the values that the cost form uses, and that
+finding them takes a call no longer on profiles whose runs never end."""
 import numpy as np
 import pytest
 
@@ -31,14 +31,18 @@ def flat(rng, M):
     return prof
 
 
-def largest_run(prof):
+def rises(prof):
+    """Of nodes 0 (the dummy slot) .. M."""
     M, dm, dd = prof["M"], prof["trans"][5].astype(int), prof["trans"][6].astype(int)
-    best = run = 0
-    for k in range(M - 1):                     # D~ of node k + 2 from D~ of node k + 1
+    out = np.zeros(M + 1, int)
+    for k in range(M - 2, -1, -1):             # D~ of node k + 2 from D~ of node k + 1
         ok = dd[k] > DEAD and dm[k] >= -MAXDM and dm[k + 1] >= -MAXDM
-        run = max(0, run + dd[k] + dm[k + 1] - dm[k]) if ok else 0
-        best = max(best, run)
-    return best
+        out[k + 1] = max(0, out[k + 2] + dd[k] + dm[k + 1] - dm[k]) if ok else 0
+    return out
+
+
+# workspace: 256 bytes, two times sixteen queues 128 bytes apart, two images
+RISES = 256 + 2 * 16 * 128 + 2 * 160 * 1024
 
 
 @pytest.mark.parametrize("M", [1, 2, 3, 100, 255, 256, 257, 511, 700, 2047, 2815])
@@ -54,8 +58,9 @@ def test_value(hm, M):
         torch.cuda.synchronize()
         aux = ws[:32].view(torch.int32).cpu().tolist()
         assert aux[1] == 1                    # within the cost form's bounds
-        assert aux[3] == largest_run(prof)
-        seen.add(aux[3])
+        got = ws[RISES:RISES + 4 * (M + 1)].view(torch.int32).cpu().numpy()
+        assert np.array_equal(got, rises(prof))
+        seen |= set(got.tolist())
     assert M < 100 or len(seen) > 2
 
 
