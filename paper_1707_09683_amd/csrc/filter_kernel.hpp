@@ -1184,7 +1184,8 @@ int occupancy_kernel(int wpb, int rows) {
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, filter_kernel<G, Q, MODE, THREADS>,
                                                      wpb * 64, lds) != hipSuccess)
         return 0;
-    return nb;
+    const int by_lds = lds_blocks(lds);
+    return nb < by_lds ? nb : by_lds;
 }
 
 template <int G, int Q, bool MSV>
@@ -1209,7 +1210,7 @@ hipError_t launch_exact(const KArgs &a, int cus, hipStream_t s) {
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    int per_cu = (int)((size_t)kLdsBytes / lds);
+    int per_cu = lds_blocks(lds);
     per_cu = per_cu < 1 ? 1 : (per_cu > 8 ? 8 : per_cu);
     hipLaunchKernelGGL((exact_kernel<QX, kExactThreads>), dim3(cus * per_cu),
                        dim3(kExactThreads), lds, s, a);

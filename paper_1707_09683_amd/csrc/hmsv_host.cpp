@@ -358,7 +358,7 @@ Cut choose_cut(const Range &r, int M, int G, int Q, int64_t ngroups, int cus, in
 // Wavefronts of a plan that fit a CU, by LDS and by registers (about Q + 60
 // per lane, 512 per SIMD lane): an estimate that queries no device.
 int resident_waves(int G, int Q, int wpb, int rows) {
-    const int by_lds = (int)((size_t)kLdsBytes / std::max<size_t>(1, lds_bytes(G, Q, rows))) * wpb;
+    const int by_lds = lds_blocks(lds_bytes(G, Q, rows)) * wpb;
     const int by_regs = Q <= 13 ? 20 : Q <= 60 ? 16 : 12;
     return std::max(wpb, std::min(by_lds, by_regs / wpb * wpb));
 }
@@ -1260,7 +1260,7 @@ void p7_choose(const hmsv_db *db, int M, hmsv_plan *plan, int cus) {
                                                            : 8;
         p.blocks = 0;
         const int by_regs = p.Q == 1 ? 32 : p.Q == 2 ? 28 : p.Q <= 8 ? 20 : 16;
-        const int by_lds = (int)((size_t)kLdsBytes / lds) * p.waves_per_block;
+        const int by_lds = lds_blocks(lds) * p.waves_per_block;
         const double resident = (double)std::max(p.waves_per_block, std::min(by_lds, by_regs));
         const double a = G / 64.0 / (4.0 * (double)cus) *
                          (total * (41.0 * p.Q + 78.0) * (1.0 + 3.0 / resident) + nseq * 2000.0);

@@ -15,6 +15,16 @@ constexpr int kRows = 21;
 constexpr int kDegenRows = 27;
 constexpr uint8_t kInvalidCode = 20;
 constexpr int kLdsBytes = 160 * 1024;
+// LDS is handed to blocks in units of 1280 bytes, which the runtime's occupancy
+// query does not round up to: of blocks of 32,256 bytes it counts five to a CU,
+// and the fifth waits for another to end.  (M = 561 on 40,000 sequences, 32 lanes
+// x 9 registers in blocks of four: 385 us with a grid of five per CU, 320 with
+// four; M = 340 on 100,000, 8 x 22: 402 and 368.)
+constexpr int kLdsUnit = 1280;
+inline int lds_blocks(size_t bytes) {
+    const size_t unit = (size_t)kLdsUnit;
+    return (int)((size_t)kLdsBytes / ((bytes + unit - 1) / unit * unit));
+}
 
 // One database sequence in processing order (longest first).
 struct SeqRec {

@@ -45,6 +45,7 @@
 // 10 to 60 residues on a profile with an I->I cost of 0, M = 100 1371 us; now
 // 189.)
 #pragma once
+#include <algorithm>
 #include "p7_kernel.hpp"
 
 namespace hmsv {
@@ -563,7 +564,7 @@ P7Blocks occupancy_p7_kernel(int wpb, int rows) {
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb.fast, p7_fast_kernel<G, Q, THREADS>,
                                                      wpb * 64, flds) != hipSuccess)
         return P7Blocks{0, 0};
-    return nb;
+    return P7Blocks{std::min(nb.general, lds_blocks(lds)), std::min(nb.fast, lds_blocks(flds))};
 }
 
 // Resident blocks of wpb wavefronts per CU (0 on error or an unsupported

@@ -50,6 +50,9 @@ int main() {
             int b = blocks;
             plan_split(&db, 0, db.nseq, &none, plan, M, &b, a, 256);
             std::printf("%d %d %d\n", b, a.nsegs, a.nlong);
+        } else if (std::sscanf(line, "lds %lld", &n) == 1) {
+            // blocks of n bytes of LDS that fit a CU
+            std::printf("%d\n", lds_blocks((size_t)n));
         } else if (std::sscanf(line, "plan %d %d %d %lld %d", &w, &M, &G, &n, &blocks) == 5) {
             // the plan and cut of filter w (0 SSV, 1 MSV, 2 P7Viterbi) at M on G compute
             // units, for `blocks` copies of n sequences of 40..1039 residues

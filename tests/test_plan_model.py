@@ -64,3 +64,10 @@ def test_part_of_a_gpu_gets_its_own_plan(driver, kind, cus):
     assert same >= len(ask) - 2, list(zip(ask, part, whole))
     # and it is not the whole GPU's plan for that database throughout
     assert part != driver([f"plan {kind} {M} 256 {n} 1" for M, n in ask])
+
+
+def test_blocks_by_lds(driver):
+    """LDS comes in units of 1280 bytes, 128 of them to a CU."""
+    for nbytes, blocks in ((1, 128), (1280, 128), (1281, 64), (26880, 6), (32256, 4), (32000, 5),
+                           (40960, 4), (40961, 3), (81920, 2), (81921, 1), (163840, 1), (163841, 0)):
+        assert int(driver([f"lds {nbytes}"])[0]) == blocks
