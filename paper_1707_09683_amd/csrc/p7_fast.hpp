@@ -541,7 +541,7 @@ hipError_t launch_p7(const P7Args &a, int wpb, P7Blocks blocks, hipStream_t s) {
     const int fn = (a.rows + kFRows) * lds_layout(G, Q, kP7Rows).RS;
     if (wpb < 1 || wpb > kP7MaxWaves<G, Q>) return hipErrorInvalidValue;
     const int nb = (n + 255) / 256, fnb = (fn + 255) / 256;
-    hipLaunchKernelGGL((p7_prep_kernel<G, Q>), dim3(nb + fnb + 1 + a.rows), dim3(256), 0, s, a, nb,
+    hipLaunchKernelGGL((p7_prep_kernel<G, Q>), dim3(nb + fnb + 2 + a.rows), dim3(256), 0, s, a, nb,
                        fnb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -188,12 +188,56 @@ __device__ __forceinline__ uint32_t p7_slot_cost(const P7Args &a, int r, int s) 
 // Per call: the LDS images (general_rows = a.rows + 7 rows of scores, and
 // a.rows + kFRows rows of the cost form, both of the lds_layout(G, Q,
 // kP7Rows) shape), one dword per thread; then one block for the profile's
-// transitions and one per emission row: what the cost form's bounds need.
+// transitions, one per emission row and one for the rises: what the cost form
+// and its bounds need.
 template <int G, int Q>
 __global__ void __launch_bounds__(256) p7_prep_kernel(P7Args a, int image_blocks,
                                                       int fimage_blocks) {
     constexpr LdsLayout D = lds_layout(G, Q, kP7Rows);
     const int check0 = image_blocks + fimage_blocks;
+    if ((int)blockIdx.x == check0 + 1 + a.rows) {
+        __shared__ int red[2][256];
+        // The rise of slot s: the largest sum of D~->D~ scores from it on (at
+        // least 0, none), rise(s) = max(0, score into s + 1 + rise(s + 1)).  Each
+        // thread takes neighbouring slots; what they make of the rise behind them
+        // is max(own, sum + it), composed over the threads behind in log2(256)
+        // steps.  A -inf score needs no case of its own: runs between them add
+        // at most the range of D->M, less than it takes.  (A walk from every
+        // slot instead, M = 2400 with D->D of 0: 12 ms a call.)
+        constexpr int slots = 2 * G * Q, per = (slots + 255) / 256;
+        const int s0 = (int)threadIdx.x * per;
+        int sc[per], own = 0, sum = 0;
+#pragma unroll
+        for (int i = per - 1; i >= 0; --i) {
+            const int s = s0 + i;             // score into slot s + 1
+            sc[i] = s + 1 < slots ? (short)p7_slot_cost(a, a.rows + kFDD, s + 1) : kP7Neg;
+            own = max(0, own + sc[i]);
+            sum += sc[i];
+        }
+        __syncthreads();
+        red[0][threadIdx.x] = own;
+        red[1][threadIdx.x] = sum;
+        __syncthreads();
+        for (int h = 1; h < 256; h *= 2) {
+            const int at = (int)threadIdx.x + h;
+            const int o = at < 256 ? red[0][at] : 0, u = at < 256 ? red[1][at] : 0;
+            __syncthreads();
+            if (at < 256) {
+                own = max(own, sum + o);
+                sum += u;
+                red[0][threadIdx.x] = own;
+                red[1][threadIdx.x] = sum;
+            }
+            __syncthreads();
+        }
+        int r = (int)threadIdx.x < 255 ? red[0][threadIdx.x + 1] : 0;
+#pragma unroll
+        for (int i = per - 1; i >= 0; --i) {
+            r = max(0, sc[i] + r);
+            if (s0 + i < slots) a.rise[s0 + i] = r;
+        }
+        return;
+    }
     if ((int)blockIdx.x > check0) {
         const int x = (int)blockIdx.x - check0 - 1;       // emission row
         bool big = false;
@@ -204,9 +248,15 @@ __global__ void __launch_bounds__(256) p7_prep_kernel(P7Args a, int image_blocks
         return;
     }
     if ((int)blockIdx.x == check0) {
-        // the transitions: max of D->M, smallest I->I cost, the rise of each
-        // slot, and whether all are within the bounds
+        // the transitions: max of D->M, smallest I->I cost, and whether all are
+        // within the bounds; and how many records the cost form takes.  (What
+        // the latter needs from memory is read first.)
         __shared__ int red[2][256];
+        __shared__ int gentle[kP7Loops];
+        const int n = p7_records(a);
+        const int step0 = (n + 255) / 256, r0 = (int)threadIdx.x * step0;
+        const int probe = a.sel && r0 < n ? a.sel[r0] : a.nseq;
+        if (threadIdx.x < kP7Loops) gentle[threadIdx.x] = (int)a.gentle[threadIdx.x];
         auto top = [&](int t) {                   // red[t][0] = the maximum
             __syncthreads();
             for (int h = 128; h > 0; h >>= 1) {
@@ -231,47 +281,6 @@ __global__ void __launch_bounds__(256) p7_prep_kernel(P7Args a, int image_blocks
         red[1][threadIdx.x] = -mii;
         bad = __syncthreads_or(bad);
         const int maxdm = top(0), minii = -top(1);
-        // The rise of slot s: the largest sum of D~->D~ scores from it on (at
-        // least 0, none), rise(s) = max(0, score into s + 1 + rise(s + 1)).  Each
-        // thread takes neighbouring slots; what they make of the rise behind them
-        // is max(own, sum + it), composed over the threads behind in log2(256)
-        // steps.  A -inf score needs no case of its own: runs between them add
-        // at most the range of D->M, less than it takes.  (A walk from every
-        // slot instead, M = 2400 with D->D of 0: 12 ms a call.)
-        {
-            constexpr int slots = 2 * G * Q, per = (slots + 255) / 256;
-            const int s0 = (int)threadIdx.x * per;
-            int sc[per], own = 0, sum = 0;
-#pragma unroll
-            for (int i = per - 1; i >= 0; --i) {
-                const int s = s0 + i;             // score into slot s + 1
-                sc[i] = s + 1 < slots ? (short)p7_slot_cost(a, a.rows + kFDD, s + 1) : kP7Neg;
-                own = max(0, own + sc[i]);
-                sum += sc[i];
-            }
-            __syncthreads();
-            red[0][threadIdx.x] = own;
-            red[1][threadIdx.x] = sum;
-            __syncthreads();
-            for (int h = 1; h < 256; h *= 2) {
-                const int at = (int)threadIdx.x + h;
-                const int o = at < 256 ? red[0][at] : 0, u = at < 256 ? red[1][at] : 0;
-                __syncthreads();
-                if (at < 256) {
-                    own = max(own, sum + o);
-                    sum += u;
-                    red[0][threadIdx.x] = own;
-                    red[1][threadIdx.x] = sum;
-                }
-                __syncthreads();
-            }
-            int r = (int)threadIdx.x < 255 ? red[0][threadIdx.x + 1] : 0;
-#pragma unroll
-            for (int i = per - 1; i >= 0; --i) {
-                r = max(0, sc[i] + r);
-                if (s0 + i < slots) a.rise[s0 + i] = r;
-            }
-        }
         if (threadIdx.x == 0) {
             a.aux[kAuxMaxDm] = maxdm;
             a.aux[kAuxTransOk] = bad ? 0 : 1;
@@ -283,13 +292,13 @@ __global__ void __launch_bounds__(256) p7_prep_kernel(P7Args a, int image_blocks
         // the first position past them, found with 256 probes at a time.  In
         // any other order some of the rest are before it: the cost form's
         // kernel sends those back one by one.
-        const int n = p7_records(a);
-        const int past = (int)a.gentle[min(max(minii, 0), kP7Loops - 1)];
+        const int past = gentle[min(max(minii, 0), kP7Loops - 1)];
         int lo = a.sel ? 0 : min(past, n), hi = a.sel ? n : lo;
         while (lo < hi) {
-            const int step = (hi - lo + 255) / 256;
+            const bool whole = hi - lo == n;
+            const int step = whole ? step0 : (hi - lo + 255) / 256;
             const int r = lo + (int)threadIdx.x * step;
-            const int k = __syncthreads_count(r < hi && a.sel[r] < past);
+            const int k = __syncthreads_count(r < hi && (whole ? probe : a.sel[r]) < past);
             hi = min(hi, lo + k * step);
             if (k > 0) lo += (k - 1) * step + 1;
         }
