@@ -507,14 +507,15 @@ void plan_split(const hmsv_db *db, int64_t first, int64_t count, const KernelEnt
     // advance unequally (the oldest of a SIMD first), and the claims that even
     // this out should have the long records.  M = 400, 500,000 sequences (7.6 per
     // group): 1784 us by the first rule, 1709 by the second; M = 100, 500,000
-    // (3.9): 517 and 490; M = 300, 250,000 (5.1): 705 and 679; M = 60, 500,000
-    // (3.1): 337 and 346.
-    // With 1.75 to 3.5 records of even lengths per group, records in order: equal
+    // (3.9): 522 and 488; M = 300, 250,000 (5.1): 678 and 670; M = 60, 500,000
+    // (3.1): 336 and 343.
+    // With 1.75 to 5 records of even lengths per group, records in order: equal
     // sums are no help there, as the oldest wavefronts then end first and leave
     // the youngest alone on their SIMDs.  50 to 500 residues, 167,000 sequences,
-    // M = 164 (2.04 per group): 266 us by the first rule, 211 in order; M = 400
-    // (2.55): 522 and 487; M = 700, 60,000 (2.9): 316 and 299; but M = 100 (1.27)
-    // 133 and 145, and lognormal lengths, M = 100, 250,000 (2.01), 274 and 292.
+    // M = 164 (2.55 per group): 236 us by the first rule, 219 in order; M = 400
+    // (2.55) 519 and 483; M = 700, 60,000 (3.7) 330 by the second and 317; but
+    // M = 100 (1.27) 132 by the first and 143, and lognormal lengths, M = 100,
+    // 250,000 (2.01), 272 and 290.
     const int64_t groups = *blocks * per_block;
     const int64_t rows = r.upto(count) + (int64_t)(a.nsegs - a.nsplit) * a.warm;
     const int64_t half = rows / groups / 2;
@@ -524,8 +525,8 @@ void plan_split(const hmsv_db *db, int64_t first, int64_t count, const KernelEnt
     const int64_t longest = std::max<int64_t>(a.nsegs > 0 ? a.seg_rows + a.warm : 0,
                                               a.nsplit < count ? r.rows(a.nsplit) : 0);
     const bool even = longest * nrec <= 2 * rows;
-    if (2 * nrec >= 7 * groups) nl = groups;
-    else if (even && 4 * nrec >= 7 * groups) nl = -1;
+    if (even && 4 * nrec >= 7 * groups && nrec < 5 * groups) nl = -1;
+    else if (2 * nrec >= 7 * groups) nl = groups;
     a.nlong = (int32_t)std::min(nl, groups);
 }
 

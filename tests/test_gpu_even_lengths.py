@@ -1,4 +1,4 @@
-"""Filter calls on sequences of even lengths, 1.75 to 3.5 records per lane group:
+"""Filter calls on sequences of even lengths, 1.75 to 5 records per lane group:
 each group takes its first records in order.  Every sequence is scored once
 and exactly at the edges of that range, and such a call is not slower for the
 number of its groups."""
@@ -40,7 +40,7 @@ def test_records_per_group(hm, filt, G, blocks, lengths):
     plan = hm.make_plan(G, -(-(M + 1) // (2 * G)), waves_per_block=4, blocks=blocks)
     N = blocks * 4 * (64 // G)
     for n in sorted({(7 * N - 1) // 4, -(-7 * N // 4), 2 * N - 1, 2 * N, 2 * N + 1, 3 * N - 1, 3 * N,
-                     3 * N + 1, (7 * N - 1) // 2, -(-7 * N // 2)}):
+                     3 * N + 1, (7 * N - 1) // 2, -(-7 * N // 2), 5 * N - 1, 5 * N}):
         L = np.full(n, 33) if lengths == "equal" else rng.integers(30, 56, n)
         if lengths == "one long":
             L[n // 3] = 150
@@ -59,9 +59,10 @@ def test_records_per_group(hm, filt, G, blocks, lengths):
 
 
 def test_time(hm):
-    """2.04 records per group (blocks of four wavefronts, five of them on a CU)
-    take no more than 1.7 (blocks of eight, three), which share the rest: 11%
-    of one record's rows more, and as much again for the spread of the runs."""
+    """2.55 records per group (blocks of four wavefronts, four of them on a CU)
+    take no more than 1.7 (blocks of eight, three) and what fewer wavefronts
+    leave exposed, 0.65 (1/16 - 1/36) of the time, 2%; 5% more for the last
+    records and 4% for the spread of the runs."""
     rng = np.random.default_rng(6)
     m, n = 164, 167_000
     L = rng.integers(50, 501, n)
@@ -81,4 +82,4 @@ def test_time(hm):
         b.record()
         torch.cuda.synchronize()
         best[w] = min(best.get(w, 1e9), a.elapsed_time(b))
-    assert best[4] < 1.15 * best[8], best
+    assert best[4] < 1.11 * best[8], best
