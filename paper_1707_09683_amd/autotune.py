@@ -8,6 +8,11 @@ that disagrees with the first one fails the run.  Results are written to
 package's ``plan_for()`` reads them.
 
 Run on the GPU:  python -m paper_1707_09683_amd.autotune [--nseq N]
+
+``--choices FILE`` times what a call without a plan chooses for itself (a
+model of its time, csrc/hmsv_host.cpp) against every other plan, over
+databases of 2,000 to 300,000 sequences, and writes both to a CSV file:
+profiles/plan_choices.csv.
 """
 from __future__ import annotations
 
@@ -40,10 +45,10 @@ def q_for(G, M):
     return (M + 1 + 2 * G - 1) // (2 * G)
 
 
-def candidates(filt, M):
+def candidates(filt, M, qmax=64):
     for G in GROUPS:
         Q = q_for(G, M)
-        if Q > QMAX[G] or lds_bytes(G, Q) > LDS_LIMIT:
+        if Q > min(qmax, QMAX[G]) or lds_bytes(G, Q) > LDS_LIMIT:
             continue
         for wpb in WAVES + ((12, 16) if G >= 32 or Q > 32 else ()):
             yield (G, Q, wpb, 0)
@@ -112,7 +117,7 @@ def write_header(path=HEADER) -> str:
     return path
 
 
-def tune(nseq=500_000, bins=M_BINS, filters=("msv", "ssv"), reps=4, seed=2, log=print):
+def tune(nseq=500_000, bins=M_BINS, filters=("msv", "ssv"), reps=4, seed=2, log=print, qmax=64):
     import torch
     import synth
     from . import Profile, Database, msv_score, ssv_score, new_workspace, make_plan
@@ -134,7 +139,7 @@ def tune(nseq=500_000, bins=M_BINS, filters=("msv", "ssv"), reps=4, seed=2, log=
             prof = Profile.from_emissions(emis, synth.BG, dev)
             ref = None
             best = None
-            for cand in candidates(filt, M):
+            for cand in candidates(filt, M, qmax):
                 plan = make_plan(*cand)
                 fn(prof, db, s, f, ws, plan)
                 torch.cuda.synchronize()
@@ -161,6 +166,86 @@ def tune(nseq=500_000, bins=M_BINS, filters=("msv", "ssv"), reps=4, seed=2, log=
     return out
 
 
+CHOICE_DBS = ((2000, "uniform"), (3000, "lognormal"), (10_000, "lognormal"), (30_000, "lognormal"),
+              (60_000, "uniform"), (100_000, "lognormal"), (167_000, "uniform"),
+              (300_000, "lognormal"))
+CHOICE_M = (30, 60, 100, 164, 250, 400, 600, 1000, 1500, 2400)
+CHOICE_FIELDS = ("kind", "M", "nseq", "lens", "plan", "us", "best", "best_us")
+
+
+def choices(path, kinds=("ssv", "p7"), log=print):
+    """Times of the plans that SSV and P7Viterbi calls choose, and of the fastest."""
+    import csv
+
+    import numpy as np
+    import torch
+    import synth
+    import paper_1707_09683_amd as hm
+
+    def timed(fn):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        fn()
+        reps, best = 1, None
+        for _ in range(4):
+            a.record()
+            for _ in range(reps):
+                fn()
+            b.record()
+            torch.cuda.synchronize()
+            us = a.elapsed_time(b) * 1e3 / reps
+            best = us if best is None else min(best, us)
+            reps = max(1, min(50, int(4000 / us)))
+        return best
+
+    out = []
+    for nseq, lens in CHOICE_DBS:
+        rng = np.random.default_rng(nseq)
+        L = synth.sample_lengths_uniform(rng, nseq, 50, 500) if lens == "uniform" else \
+            synth.sample_lengths_lognormal(rng, nseq)
+        res, off = synth.sample_residues(rng, L)
+        db = hm.Database(res, off)
+        ws = hm.new_workspace("cuda", nseq)
+        for kind in kinds:
+            dt = torch.int8 if kind == "ssv" else torch.int16
+            s = torch.empty(nseq, dtype=dt, device="cuda")
+            f = torch.empty(nseq, dtype=torch.uint8, device="cuda")
+            for M in CHOICE_M:
+                if M * nseq > (2 * 10 ** 8 if kind == "ssv" else 4 * 10 ** 7):
+                    continue
+                emis = synth.sample_emissions(rng, M)
+                if kind == "ssv":
+                    prof = hm.Profile.from_emissions(emis, synth.BG)
+                    cand = [c[:3] for c in candidates("ssv", M) if c[2] in (4, 8, 12)]
+                    chosen = hm.db_default_plan(db, "ssv", M).as_tuple()[:3]
+                else:
+                    prof = hm.P7Profile.from_probabilities(emis, synth.sample_transitions(rng, M),
+                                                           synth.BG)
+                    cand = [(G, q_for(G, M), w) for G in (4, 8, 16, 32, 64) for w in (4, 8, 16)
+                            if q_for(G, M) <= (22 if G == 64 else 16) and (w <= 8 or G == 64)]
+                    chosen = None
+                call = hm.ssv_score if kind == "ssv" else hm.p7_score
+                us = timed(lambda: call(prof, db, s, f, workspace=ws))
+                best = None
+                for c in cand:
+                    plan = hm.make_plan(*c)
+                    try:
+                        t = timed(lambda: call(prof, db, s, f, workspace=ws, plan=plan))
+                    except hm.HmsvError:
+                        continue          # not built for blocks of this size
+                    if best is None or t < best[0]:
+                        best = (t, c)
+                row = (kind, M, nseq, lens, ":".join(map(str, chosen)) if chosen else "",
+                       round(us, 1), ":".join(map(str, best[1])), round(best[0], 1))
+                out.append(row)
+                log(*row, flush=True)
+        db.close()
+    with open(path, "w", newline="") as fh:
+        w = csv.writer(fh)
+        w.writerow(CHOICE_FIELDS)
+        w.writerows(out)
+    return out
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--nseq", type=int, default=500_000)
@@ -173,19 +258,30 @@ def main():
                          "their entries")
     ap.add_argument("--emit-header", action="store_true",
                     help="only write csrc/tuned_plans.inc from tuned_plans.json")
+    ap.add_argument("--batch", action="store_true",
+                    help="tune the plans that queries of a batch start from (at most 32 "
+                         "registers per lane)")
+    ap.add_argument("--choices", default="", metavar="FILE",
+                    help="time the plans that calls choose against all others instead")
     a = ap.parse_args()
+    if a.choices:
+        sys.path.insert(0, os.path.dirname(HERE))
+        choices(a.choices)
+        return
     if a.emit_header:
         print(write_header())
         return
     sys.path.insert(0, os.path.dirname(HERE))
     t0 = time.time()
     bins = tuple(int(b) for b in a.bins.split(",")) if a.bins else M_BINS
-    res = tune(a.nseq, bins=bins, reps=a.reps, filters=tuple(a.filters.split(",")))
+    res = tune(a.nseq, bins=bins, reps=a.reps, filters=tuple(a.filters.split(",")),
+               qmax=32 if a.batch else 64)
     table = load_table() if os.path.exists(a.out) else {}
-    dev = table.setdefault(device_key(), {})
+    key = device_key() + (":batch" if a.batch else "")
+    dev = table.setdefault(key, {})
     for filt, ent in res.items():
         dev.setdefault(filt, {}).update(ent)
-    table.setdefault("_meta", {})[device_key()] = {
+    table.setdefault("_meta", {})[key] = {
         "nseq": a.nseq, "seconds": round(time.time() - t0, 1),
         "note": "fastest plan per (filter, M-bin) on a lognormal database sample"}
     with open(a.out, "w") as fh:
