@@ -109,6 +109,19 @@ uint32_t p7_lenmodel(int64_t L) {
     return (uint32_t)(uint16_t)(int16_t)loop | ((uint32_t)(uint16_t)(int16_t)move << 16);
 }
 
+// P7Args::gentle from the length models of nseq records, longest first.
+void p7_gentle(const uint32_t *lenmodel, int64_t nseq, uint32_t *gentle) {
+    for (int v = 0; v < kP7Loops; ++v) {
+        int64_t lo = v > 0 ? (int64_t)gentle[v - 1] : 0, hi = nseq;
+        while (lo < hi) {
+            const int64_t m = (lo + hi) / 2;
+            if (-(int)(int16_t)(lenmodel[m] & 0xffffu) <= v) lo = m + 1;
+            else hi = m;
+        }
+        gentle[v] = (uint32_t)lo;
+    }
+}
+
 struct Registry {
     std::vector<KernelEntry> entries;
     ExactLaunchFn exact[kMaxExactQ + 1] = {};
@@ -949,8 +962,7 @@ hmsv_status hmsv_db_create(const uint8_t *res, const int64_t *offsets, int64_t n
         recs[t].rt = (uint32_t)r | ((uint32_t)hmsv_tjb(len[i]) << 24);
         recs[t].id = (uint32_t)i;
         p7len[t] = p7_lenmodel(len[i]);
-        const int cost = -(int)(int16_t)(p7len[t] & 0xffffu);
-        if (cost < kP7Loops) p7len[np7 + (size_t)cost] = (uint32_t)(t + 1);
+
         // 16-byte aligned; the rows rounded up to 16, then 16 bytes of code 20
         // (narrow lane groups run 16 rows per step and read past the end)
         total += ((r + 15) & ~(uint64_t)15) + 16;
@@ -958,8 +970,7 @@ hmsv_status hmsv_db_create(const uint8_t *res, const int64_t *offsets, int64_t n
         cum_rows[(size_t)t + 1] = (int64_t)rows;
         if (total >= ((uint64_t)1 << 32) - 64) return HMSV_EUNSUPPORTED;
     }
-    for (int v = 1; v < kP7Loops; ++v)
-        p7len[np7 + v] = std::max(p7len[np7 + v], p7len[np7 + v - 1]);
+    p7_gentle(p7len.data(), nseq, p7len.data() + np7);
     const uint32_t pad_off = (uint32_t)total;
     const size_t bytes = (size_t)total + 64;
     std::vector<uint8_t> packed(bytes, kInvalidCode);
