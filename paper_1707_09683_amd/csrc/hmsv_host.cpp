@@ -378,12 +378,19 @@ int resident_waves(int G, int Q, int wpb, int rows) {
 
 // Wavefronts per block of an untuned plan: four, one per SIMD, unless blocks of
 // eight put more on a CU: the image decides how many blocks fit (M = 265,
-// 201,525 sequences with degenerate codes, 4 lanes of 34 registers: 713 us with
-// four, 588 with eight; M = 500, 8 lanes of 32: 950 and 895, without
-// degenerate codes 886 and 901).  More than eight lose: M = 2400 on 60,000 1.45
-// ms with 8, 1.69 with 12, 2.03 with 16 (on neighbouring records).
-int block_waves(int G, int Q, int rows) {
-    if (lds_bytes(G, Q, rows) > 40 * 1024) return 8;
+// 201,525 sequences with degenerate codes, 4 lanes of 34 registers: 667 us with
+// four, 588 with eight; M = 500, 8 lanes of 32: 950 and 896, without
+// degenerate codes 882 and 901).  Twelve where one block fits a CU and each lane
+// group of such a grid has a sequence: M = 2400 on 60,000 sequences, 32 lanes of
+// 38 1346 us with eight, 1203 with twelve, 1205 with sixteen; M = 3000 on 20,000,
+// 64 lanes of 24, 575, 533 and 587; M = 2400 on 3,000, 64 lanes of 19, 295 and
+// 311; M = 1500, 64 lanes of 12, of which two blocks of eight fit, 328, 342 and
+// 326.
+int block_waves(int G, int Q, int rows, int64_t count, int cus) {
+    const size_t lds = lds_bytes(G, Q, rows);
+    if (lds_blocks(lds) == 1)
+        return (G >= 32 || Q > 32) && count >= (int64_t)cus * 12 * (64 / G) ? 12 : 8;
+    if (lds > 40 * 1024) return 8;
     return resident_waves(G, Q, 8, rows) > resident_waves(G, Q, 4, rows) ? 8 : 4;
 }
 
@@ -423,14 +430,14 @@ hmsv_status resolve_plan(int is_msv, int M, int rows, const Range &r, const hmsv
         const bool is_tuned = G == tuned.G && p.Q == tuned.Q;
         // (the tuned block size was measured with 21 table rows)
         p.waves_per_block = is_tuned && rows == kRows ? tuned.waves_per_block
-                                                      : block_waves(G, p.Q, rows);
+                                                      : block_waves(G, p.Q, rows, r.count, cus);
         p.blocks = 0;
         double t = 0.0;
         if (r.count > 0) {
             int64_t waves = cus * resident_waves(G, p.Q, p.waves_per_block, rows);
             if (is_tuned && share == 1 && r.upto(r.count) < waves * (64 / G) * r.rows(0)) {
                 // the longest records set the end: see block_waves
-                p.waves_per_block = std::min(p.waves_per_block, block_waves(G, p.Q, rows));
+                p.waves_per_block = std::min(p.waves_per_block, block_waves(G, p.Q, rows, r.count, cus));
                 waves = cus * resident_waves(G, p.Q, p.waves_per_block, rows);
             }
             t = choose_cut(r, M, G, p.Q, waves * (64 / G), cus, share).cycles *

@@ -53,6 +53,9 @@ int main() {
         } else if (std::sscanf(line, "lds %lld", &n) == 1) {
             // blocks of n bytes of LDS that fit a CU
             std::printf("%d\n", lds_blocks((size_t)n));
+        } else if (std::sscanf(line, "waves %d %d %d %lld %d", &G, &Q, &w, &n, &blocks) == 5) {
+            // wavefronts per block of an untuned plan: w table rows, n sequences
+            std::printf("%d\n", block_waves(G, Q, w, n, blocks));
         } else if (std::sscanf(line, "plan %d %d %d %lld %d", &w, &M, &G, &n, &blocks) == 5) {
             // the plan and cut of filter w (0 SSV, 1 MSV, 2 P7Viterbi) at M on G compute
             // units, for `blocks` copies of n sequences of 40..1039 residues

@@ -71,3 +71,20 @@ def test_blocks_by_lds(driver):
     for nbytes, blocks in ((1, 128), (1280, 128), (1281, 64), (26880, 6), (32256, 4), (32000, 5),
                            (40960, 4), (40961, 3), (81920, 2), (81921, 1), (163840, 1), (163841, 0)):
         assert int(driver([f"lds {nbytes}"])[0]) == blocks
+
+
+def test_wavefronts_per_block(driver):
+    """Twelve where the image leaves one block to a CU and every lane group has a
+    sequence; no more than the kernels are built for."""
+    for G, Q, rows, n, cus, waves in ((32, 38, 21, 60000, 256, 12), (32, 38, 21, 6143, 256, 8),
+                                      (32, 38, 21, 6144, 256, 12), (32, 38, 21, 768, 32, 12),
+                                      (64, 19, 21, 3000, 256, 8), (64, 19, 21, 3072, 256, 12),
+                                      (64, 12, 21, 60000, 256, 8), (16, 61, 21, 60000, 256, 12),
+                                      (16, 18, 21, 60000, 256, 4), (4, 34, 27, 201525, 256, 8),
+                                      (8, 64, 27, 500000, 256, 12)):
+        assert int(driver([f"waves {G} {Q} {rows} {n} {cus}"])[0]) == waves, (G, Q, rows, n, cus)
+    for G, qmax in ((1, 32), (2, 64), (4, 64), (8, 64), (16, 64), (32, 60), (64, 30)):
+        for Q in range(1, qmax + 1):
+            for rows in (21, 27):
+                w = int(driver([f"waves {G} {Q} {rows} 10000000 256"])[0]) if Q % 7 == 0 else 4
+                assert w <= (16 if G >= 32 or Q > 32 else 8)
