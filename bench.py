@@ -65,9 +65,10 @@ INSTR_PER_CELL = {"msv": 0.75, "ssv": 0.75, "p7": 4.75}
 # meaningful one; this one is reported beside it.
 # P7Viterbi (Eq. 1 and the E state): per cell eight saturating adds (the
 # three transitions and the emission into M, two into I, two into D) and six
-# maxima (three for M, one each for I, D and E), 14 operations; two cells
-# per packed int16 instruction gives the 7 instructions per cell above (the
-# lazy completion of the D chains comes on top of that floor).
+# maxima (three for M, one each for I, D and E), 14 operations, two cells
+# per packed int16 instruction; the cost form does the same in the 4.75
+# instructions per cell above (the lazy completion of the D chains comes on top
+# of that floor).
 OPS_PER_CELL = {"msv": 4, "ssv": 2, "p7": 14}
 OPS_CEILING = {f: PEAK_INSTR * 2 / n for f, n in OPS_PER_CELL.items()}
 

@@ -1050,7 +1050,6 @@ __global__ void __launch_bounds__(THREADS) exact_kernel(KArgs a) {
                     const uint32_t word = k2 < 4 ? wv.x : k2 < 8 ? wv.y : k2 < 12 ? wv.z : wv.w;
                     return (word >> (8 * (k2 % 4))) & 0xffu;
                 };
-                // the step's rows; CHECK: the special states after each row
                 // the step's 16 rows; CHECK: the special states after each
                 auto step = [&](auto check_c) {
                     constexpr int N = 16;

@@ -263,7 +263,7 @@ bool tuned_plan(int kind, int M, hmsv_plan *plan) {
 // call is cut and how wide its lane groups are.  Its figures are a fit to 2,850
 // timed SSV calls (M = 30 to 2400, 2,000 to 500,000 sequences, every group
 // width, cuts at eight lengths; 11% rms error on the faster ones).  Over 74
-// other calls its choice takes 4.7% more time on average than the fastest plan,
+// other calls its choice takes 4.9% more time on average than the fastest plan,
 // 33% at most (autotune.py --choices, profiles/plan_choices.csv).
 //  * a row of a wavefront takes 6.3 Q + 13.5 cycles of its SIMD (Q registers
 //    per lane), 11% more where scores come through a ring, 15% more with
@@ -1253,7 +1253,7 @@ namespace {
 // The plan of a P7Viterbi call on a whole database: the lane group width of
 // the least expected time, T = (A^5 + B^5)^(1/5) cycles, from a fit to 1,180
 // timed calls (M = 30 to 2400, 1,000 to 400,000 sequences; 7.5% rms error; over
-// 58 others its choice takes 3.1% more than the fastest plan on average, 31%
+// 58 others its choice takes 3.2% more than the fastest plan on average, 30%
 // at most: autotune.py --choices, profiles/plan_choices.csv): A, all rows at a row's
 // issue on every SIMD, 41 Q + 78 cycles per row of a wavefront, 3/R more with
 // R wavefronts on a CU, and 2000 cycles per record; B, the longest record

@@ -31,10 +31,13 @@
 // Per pair of cells: M sub, max3, sub; I~ sub, sub, max3; D~ sub, add, max;
 // c half a max3.  200,000 lognormal sequences, p7_kernel alone and with this
 // kernel before it: M = 400 (16 lanes x 13) 8.45 -> 6.19 ms, 234 -> 167 VALU
-// instructions per wavefront row; M = 100 (8 x 7) 5.13 -> 3.75 ms, 146 -> 103
-// (half of that call is the tail of its longest records).
+// instructions per wavefront row (160 since delete chains end at their own
+// slot's bound); M = 100 (8 x 7) 5.13 -> 3.75 ms, 146 -> 103 (102; half of that
+// call is the tail of its longest records).  A last chunk of one register (Q = 13)
+// is read as 4 bytes of its 16, in four passes of the LDS: six such reads a row,
+// 15.7 bank conflict cycles.
 //
-// Conditions on the profile (p7_check, by the prep kernel): transitions <= 0,
+// Conditions on the profile (by the prep kernel): transitions <= 0,
 // emissions <= kP7Bias, tBM in [-kP7MaxTbm, 0], and D->M of every node at
 // least -kP7MaxDm unless its D->D is -inf too.  Not so: p7_kernel runs every
 // record.  Per sequence: |loop| at most the smallest I->I cost, which holds
