@@ -42,7 +42,7 @@
 // least -kP7MaxDm unless its D->D is -inf too.  Not so: p7_kernel runs every
 // record.  Per sequence: |loop| at most the smallest I->I cost, which holds
 // down to some length: this kernel lists the shorter ones for p7_kernel
-// before it starts.  And C no more than 1023 below F at the end; else its
+// as it starts.  And C no more than 1023 below F at the end; else its
 // position joins that list (sequences of non-scoring residues).  (Each short
 // one a step here and an atomic for its place in the list: 100,000 sequences of
 // 10 to 60 residues on a profile with an I->I cost of 0, M = 100 1371 us; now
@@ -87,10 +87,13 @@ __global__ void __launch_bounds__(THREADS) p7_fast_kernel(P7Args a) {
     constexpr int NCH = (Q + 3) / 4;
     constexpr bool REG = Q <= kP7RegQ;
     if (!p7_profile_fast(a)) return;          // p7_kernel runs every record
-    // the records not taken here, for p7_kernel
+    // (Read before anything is stored, these stay scalars.  After, they took two
+    // VGPRs, and 32 lanes x 16 registers past 128: M = 1000 on 500,000 sequences
+    // 36.2 ms, now 28.5.)
     const int32_t *sel = a.sel;
-    const int nseq = a.aux[kAuxFast];
-    for (int i = nseq + (int)(blockIdx.x * blockDim.x + threadIdx.x), n = p7_records(a); i < n;
+    const int nseq = a.aux[kAuxFast], minii = a.aux[kAuxMinII], all = p7_records(a);
+    // the records not taken here, for p7_kernel
+    for (int i = nseq + (int)(blockIdx.x * blockDim.x + threadIdx.x); i < all;
          i += (int)(gridDim.x * blockDim.x))
         a.pend[i - nseq] = sel ? sel[i] : i;
     extern __shared__ uint32_t lds[];
@@ -101,8 +104,6 @@ __global__ void __launch_bounds__(THREADS) p7_fast_kernel(P7Args a) {
         for (int i = threadIdx.x; i < n16; i += blockDim.x) dst[i] = src[i];
     }
     __syncthreads();
-    const int minii = a.aux[kAuxMinII];
-
     const int lane = threadIdx.x & 63;
     const int j = lane % G;
     const bool gstart = j == 0;
