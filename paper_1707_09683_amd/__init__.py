@@ -10,7 +10,6 @@ ImportError: there is no fallback implementation.
 """
 from __future__ import annotations
 
-import contextlib
 import ctypes
 from typing import NamedTuple
 import os
@@ -332,19 +331,22 @@ def new_workspace(device="cuda", nseq: int = 0) -> torch.Tensor:
     return torch.zeros(workspace_bytes(nseq), dtype=torch.uint8, device=device)
 
 
-def _scratch(device, nseq: int) -> torch.Tensor:
+def _new(n, dtype, device, stream=None) -> torch.Tensor:
+    """A tensor of a call's own, allocated on the stream that the call runs on:
+    the caching allocator hands a freed block out again as soon as the work of
+    the stream it was allocated on allows, whatever other streams still do."""
+    if stream is None:
+        return torch.empty(n, dtype=dtype, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(n, dtype=dtype, device=device)
+
+
+def _scratch(device, nseq: int, stream=None) -> torch.Tensor:
     """A workspace of one call's own.  The calls read nothing from a workspace
     that they have not written (it may be shared and is never cleared between
     calls), so it is not cleared here either: the fill of 8.7 MB and more took
     7 us, a fifth of the smallest calls."""
-    return torch.empty(workspace_bytes(nseq), dtype=torch.uint8, device=device)
-
-
-def _owner(stream):
-    """A call allocates tensors of its own on the stream that it runs on: the
-    caching allocator hands a freed block out again as soon as the work of the
-    stream it was allocated on allows, whatever other streams still do with it."""
-    return torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext()
+    return _new(workspace_bytes(nseq), torch.uint8, device, stream)
 
 
 def _score(filt, profile: Profile, db: Database, score, flags, workspace, plan, stream,
@@ -352,13 +354,12 @@ def _score(filt, profile: Profile, db: Database, score, flags, workspace, plan, 
     dev = profile.device
     n = db.nseq
     sdt = torch.uint8 if filt == "msv" else torch.int8
-    with _owner(stream):
-        if score is None:
-            score = torch.empty(n, dtype=sdt, device=dev)
-        if flags is None:
-            flags = torch.empty(n, dtype=torch.uint8, device=dev)
-        if workspace is None:
-            workspace = _scratch(dev, n)
+    if score is None:
+        score = _new(n, sdt, dev, stream)
+    if flags is None:
+        flags = _new(n, torch.uint8, dev, stream)
+    if workspace is None:
+        workspace = _scratch(dev, n, stream)
     if score.dtype != sdt or flags.dtype != torch.uint8:
         raise TypeError("score/flags dtype")
     if score.numel() < n or flags.numel() < n or not score.is_contiguous() \
@@ -496,13 +497,12 @@ def p7_score(profile: P7Profile, db: Database, score=None, flags=None, workspace
     sequence, in the database's original order."""
     dev = profile.device
     n = db.nseq
-    with _owner(stream):
-        if score is None:
-            score = torch.empty(n, dtype=torch.int16, device=dev)
-        if flags is None:
-            flags = torch.empty(n, dtype=torch.uint8, device=dev)
-        if workspace is None:
-            workspace = _scratch(dev, n)
+    if score is None:
+        score = _new(n, torch.int16, dev, stream)
+    if flags is None:
+        flags = _new(n, torch.uint8, dev, stream)
+    if workspace is None:
+        workspace = _scratch(dev, n, stream)
     if score.dtype != torch.int16 or flags.dtype != torch.uint8:
         raise TypeError("score must be int16 and flags uint8")
     if score.numel() < n or flags.numel() < n or not score.is_contiguous() \
@@ -540,13 +540,12 @@ def select(db: Database, score, flags, filt, threshold, positions=None, count=No
     n = db.nseq
     _device_tensor(score, torch.uint8 if filt == "msv" else torch.int8, n, dev, "score")
     _device_tensor(flags, torch.uint8, n, dev, "flags")
-    with _owner(stream):
-        if positions is None:
-            positions = torch.empty(max(n, 1), dtype=torch.int32, device=dev)
-        if count is None:
-            count = torch.empty(1, dtype=torch.int32, device=dev)
-        if workspace is None:
-            workspace = _scratch(dev, n)
+    if positions is None:
+        positions = _new(max(n, 1), torch.int32, dev, stream)
+    if count is None:
+        count = _new(1, torch.int32, dev, stream)
+    if workspace is None:
+        workspace = _scratch(dev, n, stream)
     _device_tensor(positions, torch.int32, n, dev, "positions")
     _device_tensor(count, torch.int32, 1, dev, "count")
     if workspace.device != dev or workspace.numel() * workspace.element_size() \
@@ -574,8 +573,7 @@ def p7_score_selected(profile: P7Profile, db: Database, positions, count, score,
     _device_tensor(score, torch.int16, n, dev, "score")
     _device_tensor(flags, torch.uint8, n, dev, "flags")
     if workspace is None:
-        with _owner(stream):
-            workspace = _scratch(dev, n)
+        workspace = _scratch(dev, n, stream)
     if workspace.device != dev or workspace.numel() * workspace.element_size() \
             < workspace_bytes(n):
         raise ValueError("workspace too small or on another device")
@@ -614,7 +612,8 @@ def pipeline(filt, profile: Profile, p7_profile: P7Profile, db: Database, thresh
     n = db.nseq
     if stream is None:
         stream = torch.cuda.current_stream(dev)
-    with _owner(stream):
+    # (see _new)
+    with torch.cuda.stream(stream):
         if workspace is None:
             workspace = _scratch(dev, n)
         fs = torch.empty(n, dtype=torch.uint8 if filt == "msv" else torch.int8, device=dev)

@@ -564,10 +564,11 @@ hmsv_status score_common(int is_msv, const hmsv_profile *prof, const hmsv_db *db
     }
     if (count == -1 && first == 0) count = db->nseq;      // whole database
     const bool in_range = first >= 0 && count >= 0 && first <= db->nseq && count <= db->nseq - first;
+    const int units = model_cus();
     hmsv_plan plan;
     st = resolve_plan(is_msv, prof->M, db->table_rows,
                       Range{db->cum_rows.data() + (in_range ? first : 0), in_range ? count : 0},
-                      plan_in, &plan, model_cus());
+                      plan_in, &plan, units);
     if (st != HMSV_OK) return st;
     const KernelEntry *e = registry().find(is_msv, plan.G, plan.Q);
     if (!e) return HMSV_ENOKERNEL;
@@ -603,7 +604,7 @@ hmsv_status score_common(int is_msv, const hmsv_profile *prof, const hmsv_db *db
     if (blocks <= 0) return HMSV_EDEVICE;
     // more work items than a launch may have
     if ((int64_t)blocks * plan.waves_per_block * 64 > (int64_t)UINT32_MAX) return HMSV_EDEVICE;
-    plan_split(db, first, count, e, plan, prof->M, &blocks, a, model_cus(), share);
+    plan_split(db, first, count, e, plan, prof->M, &blocks, a, units, share);
     // MSV: a second kernel rescores the windows the first one stored
     ExactLaunchFn xf = nullptr;
     int cus = 0;
