@@ -509,7 +509,7 @@ __global__ void __launch_bounds__(THREADS) p7_fast_kernel(P7Args a) {
 // most 18 registers or of 20: their LDS image allows one block per CU, so 16
 // wavefronts per block is the way to 4 per SIMD.  1024 threads leave 128 VGPRs:
 // p7_kernel fits them (20 to 40 bytes per lane spilt at 19, 21 and 22),
-// p7_fast_kernel spills 20 bytes per lane at 18 registers and 52 at 20.  It
+// p7_fast_kernel spills 20 bytes per lane at 18 registers and 76 at 20.  It
 // pays all the same where all CUs have work to the end: M = 2400 on 100,000
 // sequences 13.9 ms, 17.5 with 8 wavefronts (64 x 19 17.4, not built for 16),
 // M = 2200 13.2 and 17.6; not where the longest record sets it: 20,000
